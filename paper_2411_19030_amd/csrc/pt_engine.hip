@@ -456,13 +456,14 @@ __device__ __forceinline__ int lane_steps(const Consts &C, int kind) {
     }
 }
 
+// (resident lanes rely on W0 W1, R0 R1 and S0 S1 TP TQ being consecutive)
 enum { V_X = 0, V_P = 1, V_R0 = 2, V_R1 = 3, V_W0 = 4, V_W1 = 5, V_S0 = 6, V_S1 = 7, V_TP = 8, V_TQ = 9 };
 
 __device__ __forceinline__ double *group_vec(const Bufs &B, int vec, int which) {
     return B.pool + ((size_t)vec * kVecsPerLane + which) * B.pool_stride;
 }
 
-__device__ StepInfo step_info(const Consts &C, const Bufs &B, const LaunchInfo &I, const Lane &L,
+__device__ __forceinline__ StepInfo step_info(const Consts &C, const Bufs &B, const LaunchInfo &I, const Lane &L,
                               int s, const double *tpbuf) {
     StepInfo st;
     const size_t Nn = C.Nn;
@@ -711,6 +712,7 @@ __global__ void k_setup_design(const EngineDesc *__restrict__ D) {
     for (int id = t0; id < C.Nn; id += stride) B.zero[id] = 0.0;
     const int EH = C.ny + 2;
     const int total = EH * C.EW;
+    double qmin = __longlong_as_double(0x7FEFFFFFFFFFFFFFll), qmax = 0.0;
     for (int t = t0; t < total; t += stride) {
         const int py = t / C.EW, px = t - py * C.EW;
         const int ex = px - 1, ey = py - 1;
@@ -726,9 +728,20 @@ __global__ void k_setup_design(const EngineDesc *__restrict__ D) {
             B.dc[e] = C.pc * (C.c0 - C.cmin) * pow(rr, C.pc - 1.0);
             kv = kk * (1.0 / 6.0);
             cv = cc * C.cm_unit;
+            qmin = fmin(qmin, kv / cv);
+            qmax = fmax(qmax, kv / cv);
         }
         B.kq[t] = kv;
         B.cm[t] = cv;
+    }
+    // the range of the element quotients (positive doubles order as their bits)
+    for (int off = 32; off > 0; off >>= 1) {
+        qmin = fmin(qmin, __shfl_xor(qmin, off, 64));
+        qmax = fmax(qmax, __shfl_xor(qmax, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0 && qmax > 0.0) {
+        atomicMin(&B.ctl->kmin_bits, (unsigned long long)__double_as_longlong(qmin));
+        atomicMax(&B.ctl->kmax_bits, (unsigned long long)__double_as_longlong(qmax));
     }
 }
 
@@ -763,6 +776,8 @@ __global__ void k_reset_ctl(const EngineDesc *__restrict__ D, int keep_markers) 
         ctl->fwd_done = keep_markers ? f : 0;
         ctl->adj_done = 0;
         ctl->grad_scale = 1.0;
+        ctl->kmin_bits = 0x7FEFFFFFFFFFFFFFull;  // the largest double
+        ctl->kmax_bits = 0;
     }
 }
 
@@ -793,7 +808,7 @@ __global__ void k_copy_f64(double *dst, const double *src, size_t n) {
 // from the uploaded descriptor D. TIMED: per-round phase times go to the lane
 // trace (a separate instance: reading the clock is a scalar memory access, and
 // the waits for it and the timers' registers cost a round about a microsecond).
-template <int NPT, typename Real, bool MULTI, bool CMESH = false, bool TIMED = false>
+template <typename Real, bool MULTI, bool CMESH = false, bool TIMED = false>
 __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restrict__ D, Launch S,
                                                      EngineDesc E1) {
     static_assert(!(MULTI && CMESH), "coarse-mesh lanes run in single-design launches");
@@ -814,18 +829,6 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
     unsigned *bar = S.bar + (size_t)gid * kBarStride;
     double *part = S.partials + (size_t)gid * 2 * kMaxGroup * 4;
     unsigned nbar = 0;
-    const int XS = S.xch_stride;  // launch-wide halo slot length (>= H of every design)
-
-    // resident mode (NPT > 0): this workgroup's tile values of p, r, w, s live
-    // in registers across rounds, D^{-1} of the tile in LDS, x in global memory
-    // (updated in place each round); the tile's element window is staged once
-    // per lane.
-    constexpr int NR = NPT > 0 ? NPT : 1;
-    Real rp[NR], rr[NR], rw[NR], rs[NR];
-#pragma unroll
-    for (int k = 0; k < NR; ++k) rp[k] = rr[k] = rw[k] = rs[k] = 0;
-    Real *XCH = reinterpret_cast<Real *>(S.xch);
-
     // phase timers of the current lane (kept by thread 0 of rank 0, written to
     // the trace) in the TIMED instance
     constexpr bool timers = TIMED;
@@ -872,10 +875,6 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 nbar = (unsigned)r;
                 continue;
             }
-            // no register value of a resident lane outlives its lane: with
-            // them dead at the coarse-mesh call, the call saves none of them
-#pragma unroll
-            for (int k = 0; k < NR; ++k) rp[k] = rr[k] = rw[k] = rs[k] = 0;
         }
         const EngineDesc &E = [&]() -> const EngineDesc & {
             if constexpr (MULTI) return D[L.design];
@@ -908,47 +907,6 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
         Real *Sb[2] = {rv_(V_S0), rv_(V_S1)};
         Real *LZ = reinterpret_cast<Real *>(LA);  // z window of the CG rounds
         Real *LR = reinterpret_cast<Real *>(LB);  // own residuals of the CG rounds
-        Real *LD = LR;  // resident: D^{-1} of the tile (the INIT window is free after FIRST)
-        int ea_res = 0;
-        // resident: bit k set if this thread's k-th tile node is a Dirichlet node
-        // (read once per lane; a per-round byte load per node would serialise a
-        // cache round trip per node behind the unrolled stencil)
-        unsigned dmask = 0;
-        if constexpr (NPT > 0) {
-            const int a = min(rank * TS, C.Nn);
-            const int b = min(a + TS, C.Nn);
-            int elen = 0;
-            lds_sync();
-            if (a < b) {
-                elem_window(C, a, b, ea_res, elen);
-                stage_elems(B, ea_res, elen, LK, LC);
-            }
-#pragma unroll
-            for (int k = 0; k < NPT; ++k) {
-                const int id = a + (int)threadIdx.x + k * kThreads;
-                if (id < b && B.mask[id]) dmask |= 1u << k;
-            }
-            lds_sync();
-        }
-        // boundary values of r, w, s for the neighbours' halos: the first H nodes
-        // of the tile go to side 0 (read by rank-1), the last H to side 1 (rank+1)
-        auto publish = [&](int id, int a, int b, Real r, Real w, Real sv, int par) {
-            const int off = id - a;
-            if (off < H && rank > 0) {
-                Real *base = XCH + (((size_t)blockIdx.x * 2 + par) * 2 + 0) * 3 * XS;
-                stc(base + off, r);
-                stc(base + XS + off, w);
-                stc(base + 2 * XS + off, sv);
-            }
-            const int o2 = off - ((b - a) - H);
-            if (o2 >= 0 && rank < g - 1) {
-                Real *base = XCH + (((size_t)blockIdx.x * 2 + par) * 2 + 1) * 3 * XS;
-                stc(base + o2, r);
-                stc(base + XS + o2, w);
-                stc(base + 2 * XS + o2, sv);
-            }
-        };
-        (void)publish;
         auto barrier = [&](bool release) -> bool {
             ++nbar;
             if constexpr (!timers) {
@@ -1230,50 +1188,6 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
         };
         (void)gmg_round;
 
-        // Resident rounds: the raw halo values (r, w, s of the neighbours'
-        // boundary nodes) for the next round are loaded right after the
-        // barrier, together with the partial sums, so both round trips overlap;
-        // the halo z is formed once alpha and beta are known, with D^{-1} of the
-        // halo nodes staged in LDS once per solve (FIRST).
-        constexpr int kHP = 2;
-        Real hpr[kHP], hpw[kHP], hps[kHP];
-        bool hp_ok = false;
-        auto halo_prefetch = [&](const StepInfo &st, bool need_s) {
-            if constexpr (NPT > 0) {
-                const int a = min(rank * TS, C.Nn);
-                const int b = min(a + TS, C.Nn);
-                const int ppar = (nbar - 1) & 1;  // parity of the round just published
-                hp_ok = 2 * H <= kThreads * kHP;
-                // per-call index math: hoisted out of the lane loop it would be
-                // held in spilled registers, and each reload would wait for the
-                // halo loads already in flight
-                int tid = threadIdx.x;
-                asm volatile("" : "+v"(tid));
-#pragma unroll
-                for (int u = 0; u < kHP; ++u) {
-                    const int q = tid + u * kThreads;
-                    hpr[u] = hpw[u] = hps[u] = (Real)0;
-                    if (hp_ok && q < 2 * H) {
-                        const bool left = q < H;
-                        const int id = left ? a - H + q : b + (q - H);
-                        if (id >= 0 && id < C.Nn) {
-                            const int nb = left ? blockIdx.x - 1 : blockIdx.x + 1;
-                            const int k = left ? q : q - H;
-                            const Real *base =
-                                XCH + (((size_t)nb * 2 + ppar) * 2 + (left ? 1 : 0)) * 3 * XS;
-                            hpr[u] = ldc(base + k);
-                            hpw[u] = ldc(base + XS + k);
-                            if (need_s) hps[u] = ldc(base + 2 * XS + k);
-                        }
-                    }
-                }
-            } else {
-                (void)st;
-                (void)need_s;
-            }
-        };
-        (void)halo_prefetch;
-
         const bool is_adj = is_adjoint_kind(L.kind);
         const bool tracer = (rank == 0 && threadIdx.x == 0);
         unsigned long long *trec = S.trace + (size_t)lane_id * S.trace_stride;
@@ -1369,7 +1283,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                         B.out_T[(size_t)C.Nn + id] = tpv;
                     }
                 };
-                if (NPT == 0 && C.gmg) {
+                if (C.gmg) {
                     // multigrid lanes: the node ranges the multigrid rounds own, in
                     // chunks whose operand windows (C/delta operand and x0, one
                     // grid row of halo) are staged in LDS; rows of very wide
@@ -1564,67 +1478,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 const double ms = st.fine ? C.inv_dt : C.inv_dtau;
                 const double *dinv = st.fine ? B.dinv_f : B.dinv_c;
                 double loc[2] = {0.0, 0.0};
-                if constexpr (NPT > 0) {
-                // resident: one tile per workgroup; r0, w0, x, dinv stay in registers
-                {
-                    const int a = min(rank * TS, C.Nn);
-                    const int b = min(a + TS, C.Nn);
-                    const int lo = a - H;
-                    const int len = (b - a) + 2 * H;
-                    lds_sync();
-                    for (int q0 = threadIdx.x; q0 < len; q0 += kThreads * kU) {
-                        Real rv[kU], dv[kU];
-#pragma unroll
-                        for (int u = 0; u < kU; ++u) {
-                            const int q = q0 + u * kThreads;
-                            const int id = lo + q;
-                            const bool in = q < len && id >= 0 && id < C.Nn;
-                            rv[u] = in ? ldc(Rb[0] + id) : (Real)0;
-                            dv[u] = in ? (Real)dinv[id] : (Real)0;
-                        }
-#pragma unroll
-                        for (int u = 0; u < kU; ++u) {
-                            const int q = q0 + u * kThreads;
-                            const int id = lo + q;
-                            if (q < len) {
-                                LZ[q] = dv[u] * rv[u];
-                                if (id >= a && id < b) LR[id - a] = rv[u];
-                                // D^{-1} of the halo nodes, behind the tile's own
-                                // (left halo first): fixed for the whole solve
-                                else LR[TS + (q < H ? q : q - (b - a))] = dv[u];
-                            }
-                        }
-                    }
-                    lds_sync();
-                    const int par = nbar & 1;
-                    int tid = threadIdx.x;
-                    asm volatile("" : "+v"(tid));  // per-round index math (not hoisted)
-#pragma unroll
-                    for (int k = 0; k < NPT; ++k) {
-                        const int id = a + tid + k * kThreads;
-                        rp[k] = rs[k] = 0.0;
-                        if (id < b) {
-                            const int li2 = id - lo;
-                            Real w = 0;
-                            if (!((dmask >> k) & 1u)) {
-                                const int j = id / C.W, i = id - j * C.W;
-                                const CoefT<Real> aa = node_coef_t<Real>(C, LK, LC, ea_res, i, j, ms, 1.0);
-                                w = apply_t<Real>(aa, LZ, li2, C.W);
-                            }
-                            rr[k] = LR[id - a];
-                            LD[id - a] = (Real)dinv[id];
-                            rw[k] = w;
-                            const Real z = LZ[li2];
-                            loc[0] += (double)rr[k] * (double)z;
-                            loc[1] += (double)z * (double)w;
-                            publish(id, a, b, rr[k], rw[k], (Real)0, par);
-                        } else {
-                            rr[k] = rw[k] = 0.0;
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                } else if (C.gmg) {
+                if (C.gmg) {
                     ok = gmg_round(st, false, true, 0.0, 0.0, loc, 2);
                     if (!ok) break;
                 } else {
@@ -1681,7 +1535,6 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 }
                 ok = barrier(false);
                 if (!ok) break;
-                if constexpr (NPT > 0) halo_prefetch(st, false);
                 double tot[2];
                 group_sum<2>(all_part(par), g, tot, red);
                 mark_red();
@@ -1696,99 +1549,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 const bool first = (i0 == 0);
                 const double al = c.alpha, be = c.beta;
                 double loc[3] = {0.0, 0.0, 0.0};
-                if constexpr (NPT > 0) {
-                // resident: halo of z_{i+1} rebuilt from the neighbours' published
-                // r_i, w_i, s_{i-1}; own values updated in registers
-                {
-                    const int a = min(rank * TS, C.Nn);
-                    const int b = min(a + TS, C.Nn);
-                    const int lo = a - H;
-                    const int ppar = (nbar - 1) & 1;  // parity of the previous round
-                    int tid = threadIdx.x;
-                    asm volatile("" : "+v"(tid));  // per-round index math (not hoisted)
-                    // x of the tile is read only by its owning thread during
-                    // the rounds (plain loads of its own device-coherent stores)
-                    double xo[NR];
-#pragma unroll
-                    for (int k = 0; k < NPT; ++k) {
-                        const int id = a + tid + k * kThreads;
-                        xo[k] = id < b ? X[id] : 0.0;
-                    }
-                    lds_sync();
-                    if (hp_ok) {
-#pragma unroll
-                        for (int u = 0; u < kHP; ++u) {
-                            const int q = tid + u * kThreads;
-                            if (q < 2 * H) {
-                                const Real sv = first ? hpw[u] : hpw[u] + (Real)be * hps[u];
-                                const Real z = LD[TS + q] * (hpr[u] - (Real)al * sv);
-                                LZ[q < H ? q : (b - lo) + (q - H)] = z;
-                            }
-                        }
-                    } else
-                    for (int q = threadIdx.x; q < 2 * H; q += kThreads) {
-                        const bool left = q < H;
-                        const int id = left ? a - H + q : b + (q - H);
-                        Real z = 0;
-                        if (id >= 0 && id < C.Nn) {
-                            const int nb = left ? blockIdx.x - 1 : blockIdx.x + 1;
-                            const int k = left ? q : q - H;
-                            const Real *base =
-                                XCH + (((size_t)nb * 2 + ppar) * 2 + (left ? 1 : 0)) * 3 * XS;
-                            const Real rh = ldc(base + k);
-                            const Real wh = ldc(base + XS + k);
-                            const Real sh = first ? (Real)0 : ldc(base + 2 * XS + k);
-                            const Real sv = first ? wh : wh + (Real)be * sh;
-                            z = LD[TS + q] * (rh - (Real)al * sv);
-                        }
-                        LZ[left ? q : (b - lo) + (q - H)] = z;
-                    }
-                    // all x loads done before the first x store: with stores in
-                    // flight the compiler can only wait for a load by draining
-                    // the stores too (loads and stores share one counter), i.e.
-                    // one store round trip per node
-                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-#pragma unroll
-                    for (int k = 0; k < NPT; ++k) {
-                        const int id = a + tid + k * kThreads;
-                        if (id < b) {
-                            const Real dk = LD[id - a];
-                            const Real zi = dk * rr[k];
-                            const Real pn = first ? zi : zi + (Real)be * rp[k];
-                            const Real sn = first ? rw[k] : rw[k] + (Real)be * rs[k];
-                            stc(X + id, xo[k] + al * (double)pn);
-                            rr[k] -= (Real)al * sn;
-                            rp[k] = pn;
-                            rs[k] = sn;
-                            LZ[id - lo] = dk * rr[k];
-                        }
-                    }
-                    lds_sync();
-                    const int par = nbar & 1;
-#pragma unroll
-                    for (int k = 0; k < NPT; ++k) {
-                        const int id = a + tid + k * kThreads;
-                        if (id < b) {
-                            const int li2 = id - lo;
-                            Real w = 0;
-                            if (!((dmask >> k) & 1u)) {
-                                const int j = id / C.W, i = id - j * C.W;
-                                const CoefT<Real> aa = node_coef_t<Real>(C, LK, LC, ea_res, i, j, ms, 1.0);
-                                w = apply_t<Real>(aa, LZ, li2, C.W);
-                            }
-                            rw[k] = w;
-                            const Real z = LZ[li2];
-                            loc[0] += (double)rr[k] * (double)z;
-                            loc[1] += (double)z * (double)w;
-                            loc[2] += (double)rr[k] * (double)rr[k];
-                            publish(id, a, b, rr[k], rw[k], rs[k], par);
-                        }
-                        // keep the unrolled node iterations from being interleaved
-                        // (register pressure)
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                } else if (C.gmg) {
+                if (C.gmg) {
                     // its own array: passing loc's address keeps loc in scratch
                     // memory in every round form, stored on every node
                     double gl[3] = {0.0, 0.0, 0.0};
@@ -1894,7 +1655,6 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 }
                 ok = barrier(false);
                 if (!ok) break;
-                if constexpr (NPT > 0) halo_prefetch(st, true);
                 double tot[3];
                 group_sum<3>(all_part(par), g, tot, red);
                 mark_red();
@@ -1946,8 +1706,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                     const int a = t * TS;
                     const int b = min(a + TS, C.Nn);
                     for (int id = a + threadIdx.x; id < b; id += kThreads) {
-                        // resident: the owning thread of the rounds reads its own x
-                        const double x = zx ? 0.0 : (NPT > 0 ? X[id] : ldc(X + id));
+                        const double x = zx ? 0.0 : ldc(X + id);
                         switch (L.kind) {
                             case F_PRI: {
                                 if (double *Sj = srow(C, B, st.j, nullptr)) Sj[id] = x;
@@ -2103,6 +1862,12 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
         set_status(ctl, -3);
     }
 }
+
+}  // namespace pt
+
+#include "pt_resident.hip"
+
+namespace pt {
 
 // After the primal engine (blockIdx.y = design): u_0 = 0, Theta, and the
 // N_tau = 1 case. With G = 0, Theta~ is the sum of the slices' parts in slice

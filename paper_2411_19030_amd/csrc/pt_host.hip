@@ -237,18 +237,17 @@ void carve_design(Carver &c, const pt_problem *p, DesignLayout &L, bool batched)
 
 // Launch-wide arrays of an engine launch.
 struct SharedLayout {
-    size_t desc, bar, flags, partials, wg_group, groups, lanes, qhead, qslot, pool, trace, xch;
+    size_t desc, bar, flags, partials, wg_group, groups, lanes, qhead, qslot, pool, trace;
     size_t gvec, gvec_stride;
-    int max_lanes, max_groups, trace_stride, xch_stride;
+    int max_lanes, max_groups, trace_stride;
     size_t pool_stride;
 };
 
 void carve_shared(Carver &c, SharedLayout &S, int n_designs, int max_lanes, int max_groups,
-                  size_t pool_stride, int trace_stride, int xch_stride, size_t gmg_nodes) {
+                  size_t pool_stride, int trace_stride, size_t gmg_nodes) {
     S.max_lanes = max_lanes;
     S.max_groups = max_groups;
     S.trace_stride = trace_stride;
-    S.xch_stride = xch_stride;
     S.pool_stride = pool_stride;
     S.desc = c.take(sizeof(EngineDesc) * n_designs);
     S.bar = c.take(sizeof(unsigned) * kMaxGroups * kBarStride);
@@ -261,7 +260,6 @@ void carve_shared(Carver &c, SharedLayout &S, int n_designs, int max_lanes, int 
     S.qslot = c.take(sizeof(int) * kMaxGroups);
     S.pool = c.take(sizeof(double) * (size_t)max_groups * kVecsPerLane * pool_stride);
     S.trace = c.take(sizeof(unsigned long long) * (size_t)max_lanes * trace_stride);
-    S.xch = c.take(sizeof(double) * (size_t)kMaxGrid * 12 * xch_stride);
     // multigrid level vectors r, u_a, u_b of levels >= 1 per group
     S.gvec_stride = 3 * gmg_nodes;
     S.gvec = c.take(sizeof(double) * (size_t)max_groups * S.gvec_stride + sizeof(double));
@@ -292,7 +290,7 @@ Layout layout(const pt_problem *p) {
     carve_design(c, p, L.d, false);
     const int max_lanes = 2 * p->n_slices + 2;
     carve_shared(c, L.s, 1, max_lanes, max_groups_of(p), (size_t)(p->nx + 1) * (p->ny + 1),
-                 trace_stride_of(p), p->nx + 2, (size_t)hierarchy(p).nodes);
+                 trace_stride_of(p), (size_t)hierarchy(p).nodes);
     L.total = c.o;
     return L;
 }
@@ -309,17 +307,16 @@ BatchLayout batch_layout(int n, const pt_problem *probs) {
     BatchLayout L{};
     L.d.resize(n);
     Carver c;
-    int lanes = 0, tstride = TR_HDR, xs = 2;
+    int lanes = 0, tstride = TR_HDR;
     size_t max_nn = 1, max_gn = 0;
     for (int k = 0; k < n; ++k) {
         carve_design(c, &probs[k], L.d[k], true);
         max_gn = std::max(max_gn, (size_t)hierarchy(&probs[k]).nodes);
         lanes += 2 * probs[k].n_slices + 2;
         tstride = std::max(tstride, trace_stride_of(&probs[k]));
-        xs = std::max(xs, probs[k].nx + 2);
         max_nn = std::max(max_nn, (size_t)(probs[k].nx + 1) * (probs[k].ny + 1));
     }
-    carve_shared(c, L.s, n, lanes, kMaxBatchGroups, max_nn, tstride, xs, max_gn);
+    carve_shared(c, L.s, n, lanes, kMaxBatchGroups, max_nn, tstride, max_gn);
     L.max_nn = max_nn;
     L.total = c.o;
     return L;
@@ -471,8 +468,6 @@ Launch make_launch(void *ws, const SharedLayout &S, Control *ctl0, long long tim
     X.lanes = at<Lane>(ws, S.lanes);
     X.bar = at<unsigned>(ws, S.bar);
     X.partials = at<double>(ws, S.partials);
-    X.xch = at<double>(ws, S.xch);
-    X.xch_stride = S.xch_stride;
     X.qhead = at<unsigned>(ws, S.qhead);
     X.qslot = at<int>(ws, S.qslot);
     X.trace = at<unsigned long long>(ws, S.trace);
@@ -592,40 +587,34 @@ int tile_for(int Nn, int nwg, int H, int cap_doubles, int tile_max) {
     return ts;
 }
 
-const void *engine_kernel(bool fp32, int npt, bool multi, bool cmesh = false, bool timed = false) {
-    if (timed)  // FP64 single-design launches without coarse-mesh lanes; resident: 8 nodes
-        return npt == 0 ? (const void *)k_engine<0, double, false, false, true>
-                        : (const void *)k_engine<8, double, false, false, true>;
-    if (cmesh) {
-        // coarse-mesh launches: resident lanes always take the 8-node form
-        if (fp32) return npt == 0 ? (const void *)k_engine<0, float, false, true>
-                                  : (const void *)k_engine<8, float, false, true>;
-        return npt == 0 ? (const void *)k_engine<0, double, false, true>
-                        : (const void *)k_engine<8, double, false, true>;
+// Which engine kernel a launch takes. Resident lanes compute in FP64 at either
+// precision: their vectors never leave the chip, so FP32 would save no traffic.
+struct Engine {
+    bool resident, fp32, multi, cmesh, timed;
+};
+
+const void *engine_kernel(const Engine &K) {
+    if (K.resident) {
+        if (K.timed) return (const void *)k_resident<false, false, true>;
+        if (K.cmesh) return (const void *)k_resident<false, true, false>;
+        return K.multi ? (const void *)k_resident<true, false, false>
+                       : (const void *)k_resident<false, false, false>;
     }
-    if (multi) {
-        if (fp32) return npt == 0 ? (const void *)k_engine<0, float, true>
-                                  : (const void *)k_engine<8, float, true>;
-        return npt == 0 ? (const void *)k_engine<0, double, true>
-                        : (const void *)k_engine<8, double, true>;
-    }
-    if (fp32)
-        return npt == 0   ? (const void *)k_engine<0, float, false>
-               : npt == 1 ? (const void *)k_engine<1, float, false>
-               : npt == 2 ? (const void *)k_engine<2, float, false>
-               : npt == 4 ? (const void *)k_engine<4, float, false>
-                          : (const void *)k_engine<8, float, false>;
-    return npt == 0   ? (const void *)k_engine<0, double, false>
-           : npt == 1 ? (const void *)k_engine<1, double, false>
-           : npt == 2 ? (const void *)k_engine<2, double, false>
-           : npt == 4 ? (const void *)k_engine<4, double, false>
-                      : (const void *)k_engine<8, double, false>;
+    if (K.timed)  // FP64 single-design launches without coarse-mesh lanes
+        return (const void *)k_engine<double, false, false, true>;
+    if (K.cmesh)
+        return K.fp32 ? (const void *)k_engine<float, false, true>
+                      : (const void *)k_engine<double, false, true>;
+    if (K.multi)
+        return K.fp32 ? (const void *)k_engine<float, true>
+                      : (const void *)k_engine<double, true>;
+    return K.fp32 ? (const void *)k_engine<float, false>
+                  : (const void *)k_engine<double, false>;
 }
 
 // Workgroups of the engine that fit on the device at once.
-int engine_capacity(bool fp32, int npt, bool multi, size_t lds_bytes, const Device &dev,
-                    int &cap, bool cmesh = false, bool timed = false) {
-    const void *kern = engine_kernel(fp32, npt, multi, cmesh, timed);
+int engine_capacity(const Engine &K, size_t lds_bytes, const Device &dev, int &cap) {
+    const void *kern = engine_kernel(K);
     PT_TRY(hip_ok(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)lds_bytes)));
     int occ = 0;
@@ -643,14 +632,13 @@ static_assert(sizeof(EngineDesc) + sizeof(Launch) + sizeof(void *) <= 4096,
 
 // single: the descriptor of a single-design launch (passed by value), or
 // nullptr for a multi-design launch that reads D.
-int launch_engine(bool fp32, int npt, const EngineDesc *D, const EngineDesc *single,
+int launch_engine(const Engine &K, const EngineDesc *D, const EngineDesc *single,
                   const Launch &X, int grid, size_t lds_bytes, const Device &dev,
-                  hipStream_t stream, bool cmesh = false, bool timed = false) {
-    const bool multi = single == nullptr;
+                  hipStream_t stream) {
     int cap = 0;
-    PT_TRY(engine_capacity(fp32, npt, multi, lds_bytes, dev, cap, cmesh, timed));
+    PT_TRY(engine_capacity(K, lds_bytes, dev, cap));
     if (cap < grid || grid > kMaxGrid) return PT_ESIZE;
-    const void *kern = engine_kernel(fp32, npt, multi, cmesh, timed);
+    const void *kern = engine_kernel(K);
     Launch Xv = X;
     const EngineDesc *Dv = D;
     EngineDesc E1;
@@ -686,18 +674,26 @@ int reset_launch_state(void *ws, const SharedLayout &S, int n_designs, hipStream
 // with slices s0 + r*gstride + k*lstride, k = 0..nlanes-1, kept if within
 // [smin, smax]. Built on the device from this kernel argument, so no host
 // buffer must outlive the call.
+// How a lane is cut up on its group: nodes per streaming tile, or the rectangle,
+// polynomial degree and window rows per thread of a resident lane.
+struct Shape {
+    int tile, tw, th, deg, nr;
+};
+
 struct Run {
-    int kind, ngroups, nwg, tile, s0, gstride, lstride, nlanes, smin, smax;
+    int kind, ngroups, nwg, s0, gstride, lstride, nlanes, smin, smax;
     int lead_kind, lead_slice;  // a lane run first by every group of the run (kind < 0: none)
+    Shape shape, lead_shape;
 };
 
 // Groups of one shape taking two kinds of lanes from shared queue 0, in the
 // order the correction sweep consumes them: slice by slice along dirA, lane
 // kind A before kind B of the same slice.
 struct QueueArgs {
-    int ngroups, nwg, tile;
+    int ngroups, nwg;
     int kindA, nA, sA0, dirA;
     int kindB, nB, sB0, dirB;
+    Shape shapeA, shapeB;
     int lagB;  // B's slice n goes after A's slice n + lagB along the sweep
 };
 
@@ -707,6 +703,17 @@ struct PlanArgs {
     Run run[6];
     QueueArgs Q;
 };
+
+__device__ void put_lane(Lane *l, int kind, int slice, int design, const Shape &s) {
+    l->kind = kind;
+    l->slice = slice;
+    l->design = design;
+    l->tile = s.tile;
+    l->tw = s.tw;
+    l->th = s.th;
+    l->deg = s.deg;
+    l->nr = s.nr;
+}
 
 __global__ void k_build_plan(PlanArgs P, Group *groups, Lane *lanes, int *wg_group) {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
@@ -722,19 +729,13 @@ __global__ void k_build_plan(PlanArgs P, Group *groups, Lane *lanes, int *wg_gro
             G.lane0 = lidx;
             int n = 0;
             if (R.lead_kind >= 0) {
-                lanes[lidx].kind = R.lead_kind;
-                lanes[lidx].slice = R.lead_slice;
-                lanes[lidx].design = 0;
-                lanes[lidx].tile = R.tile;
+                put_lane(lanes + lidx, R.lead_kind, R.lead_slice, 0, R.lead_shape);
                 ++n;
             }
             for (int k = 0; k < R.nlanes; ++k) {
                 const int sl = R.s0 + q * R.gstride + k * R.lstride;
                 if (sl < R.smin || sl > R.smax) continue;
-                lanes[lidx + n].kind = R.kind;
-                lanes[lidx + n].slice = sl;
-                lanes[lidx + n].design = 0;
-                lanes[lidx + n].tile = R.tile;
+                put_lane(lanes + lidx + n, R.kind, sl, 0, R.shape);
                 ++n;
             }
             G.nlanes = n;
@@ -754,10 +755,8 @@ __global__ void k_build_plan(PlanArgs P, Group *groups, Lane *lanes, int *wg_gro
             const int sa = Q.sA0 + Q.dirA * ia, sb = Q.sB0 + Q.dirB * ib;
             const bool takeA =
                 ib >= Q.nB || (ia < Q.nA && Q.dirA * sa <= Q.dirA * sb + Q.lagB);
-            lanes[lidx].kind = takeA ? Q.kindA : Q.kindB;
-            lanes[lidx].slice = takeA ? sa : sb;
-            lanes[lidx].design = 0;
-            lanes[lidx].tile = Q.tile;
+            put_lane(lanes + lidx, takeA ? Q.kindA : Q.kindB, takeA ? sa : sb, 0,
+                     takeA ? Q.shapeA : Q.shapeB);
             ++lidx;
             if (takeA) ++ia;
             else ++ib;
@@ -791,6 +790,160 @@ struct LanePlan {
     int lead_kind = -1, lead_slice = 0;  // a lane the group runs first (one group only)
 };
 
+// ---------------------------------------------------------------------------
+// Shapes of resident lanes
+// ---------------------------------------------------------------------------
+
+// Window rows per thread the kernel is built for.
+constexpr int kResRowChoices[] = {2, 4, 6};
+static_assert(kResRowChoices[2] == kResRows, "the largest variant");
+constexpr int kResMaxColumns = 480;  // window columns: two rim cells per thread at most
+
+// LDS bytes of a resident lane: two operand windows with a rim and two values
+// per node slot (the p and x of the solve).
+size_t res_lds_bytes(const Shape &s, int W, int HN) {
+    const int hx = s.tw < W ? s.deg + 1 : 0, hy = s.th < HN ? s.deg + 1 : 0;
+    const int wc = s.tw + 2 * hx, wr = s.th + 2 * hy;
+    const int nq = std::min(kThreads / wc, (wr + s.nr - 1) / s.nr);
+    return sizeof(double) * (2 * (size_t)(wc + 2) * (nq * s.nr + 2) + 2 * (size_t)s.nr * kThreads);
+}
+
+// The rectangles for a grid of W x HN nodes on at most max_wg workgroups: the
+// fewest window rows per thread, then the smallest window. False if the grid
+// does not fit. `wgs`: the workgroups used.
+bool res_shape(int W, int HN, int max_wg, int deg, int rows_max, size_t lds_cap, Shape &best,
+               int &wgs) {
+    for (int nr : kResRowChoices) {
+        if (nr > rows_max) break;
+        double best_cost = INFINITY;
+        for (int TX = 1; TX <= std::min(max_wg, W); ++TX) {
+            const int tw = (W + TX - 1) / TX;
+            if ((W + tw - 1) / tw != TX) continue;  // the same width with fewer columns
+            const int wc = tw + (TX > 1 ? 2 * (deg + 1) : 0);
+            if (wc > kResMaxColumns) continue;
+            const int th = (HN + std::min(max_wg / TX, HN) - 1) / std::min(max_wg / TX, HN);
+            const int TY = (HN + th - 1) / th;
+            const int wr = th + (TY > 1 ? 2 * (deg + 1) : 0);
+            if (wr > kThreads / wc * nr) continue;
+            const Shape s{0, tw, th, deg, nr};
+            if (res_lds_bytes(s, W, HN) > lds_cap) continue;
+            const double cost = (double)wc * wr;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = s;
+                wgs = TX * TY;
+            }
+        }
+        if (best_cost < INFINITY) return true;
+    }
+    return false;
+}
+
+// The fewest workgroups that hold the grid (0: none do).
+int res_min_wgs(int W, int HN, int deg, int rows_max, size_t lds_cap) {
+    int best = 0;
+    for (int nr : kResRowChoices) {
+        if (nr > rows_max) break;
+        for (int TX = 1; TX <= W && (best == 0 || TX < best); ++TX) {
+            const int tw = (W + TX - 1) / TX;
+            const int wc = tw + (TX > 1 ? 2 * (deg + 1) : 0);
+            if (wc > kResMaxColumns) continue;
+            const int wr = kThreads / wc * nr;
+            const int th = HN <= wr ? HN : wr - 2 * (deg + 1);
+            if (th < 1 || res_lds_bytes(Shape{0, tw, th, deg, nr}, W, HN) > lds_cap) continue;
+            const int n = TX * ((HN + th - 1) / th);
+            if (best == 0 || n < best) best = n;
+        }
+    }
+    return best;
+}
+
+// Plans a launch whose lanes are all resident: group counts and sizes and the
+// lanes' shapes. False if the lanes do not fit the grid.
+bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt_tuning &T,
+                   int grid, int lds_cap_d, int sweep_wgs, const CoarseMesh *cm,
+                   std::vector<int> &ngroups, std::vector<int> &nwg, std::vector<Shape> &shape,
+                   std::vector<Shape> &lead_shape, size_t &lds) {
+    const int HN = C.ny + 1;
+    const size_t cap = (size_t)lds_cap_d * sizeof(double);
+    const int rows_max = std::max(2, T.resident_npt_max);
+    const int deg_f = 3, deg_c = 4;
+    auto deg_of = [&](int kind) {
+        if (kind == F_PRI || kind == F_ADJ) return deg_f;
+        return C.coarse_iters > 0 ? 0 : deg_c;
+    };
+    auto fit = [&](int kind, int max_wg, Shape &s, int &n) {
+        return res_shape(C.W, HN, max_wg, deg_of(kind), rows_max, cap, s, n);
+    };
+    auto min_wgs = [&](int kind) { return res_min_wgs(C.W, HN, deg_of(kind), rows_max, cap); };
+    // the least workgroups that hold the grid for every kind of batched lane
+    int g_min = 0, nb = 0, lanes = 0, lat = 0;
+    for (size_t k = 0; k < plans.size(); ++k) {
+        const LanePlan &p = plans[k];
+        if (p.latency || p.count == 0) continue;
+        ++nb;
+        lanes += p.count;
+        if (is_cm_kind(p.kind)) continue;
+        const int g = min_wgs(p.kind);
+        if (g == 0 || g > grid) return false;
+        g_min = std::max(g_min, g);
+    }
+    lds = 0;
+    // sequential sweeps on groups of their own
+    for (size_t k = 0; k < plans.size(); ++k) {
+        const LanePlan &p = plans[k];
+        ngroups[k] = 0;
+        nwg[k] = 1;
+        if (!p.latency || p.count == 0) continue;
+        const int want = p.fixed_nwg > 0 ? p.fixed_nwg : std::min(sweep_wgs, grid / 4);
+        int n = want;
+        if (is_cm_kind(p.kind)) shape[k] = Shape{0, 0, 0, 0, 0};
+        else if (!fit(p.kind, std::max(want, min_wgs(p.kind)), shape[k], n)) return false;
+        if (p.lead_kind >= 0) {
+            int m = 0;
+            if (!fit(p.lead_kind, std::max(n, min_wgs(p.lead_kind)), lead_shape[k], m))
+                return false;
+            n = std::max(n, m);
+            lds = std::max(lds, res_lds_bytes(lead_shape[k], C.W, HN));
+        }
+        if (!is_cm_kind(p.kind)) lds = std::max(lds, res_lds_bytes(shape[k], C.W, HN));
+        ngroups[k] = p.count;
+        nwg[k] = n;
+        lat += n * p.count;
+    }
+    // the rest of the grid for the batched lanes, on groups of one size
+    int avail = g_min > 0 ? (grid - lat) / g_min : nb;
+    if (avail < nb) return false;
+    avail = std::min(avail, lanes);
+    const int gsz = g_min > 0 ? std::max(g_min, (grid - lat) / std::max(1, avail)) : 1;
+    int left = avail, kinds = nb;
+    double wF = 0.0;
+    for (const auto &p : plans)
+        if (!p.latency && p.count > 0) wF += p.weight * p.count;
+    int used_max = 1;
+    for (size_t k = 0; k < plans.size(); ++k) {
+        const LanePlan &p = plans[k];
+        if (p.latency || p.count == 0) continue;
+        --kinds;
+        int q = p.queues > 0 ? p.queues : (int)floor(avail * p.weight * p.count / wF);
+        q = std::max(1, std::min(q, std::min(p.count, left - kinds)));
+        ngroups[k] = q;
+        left -= q;
+        int n = 1;
+        if (is_cm_kind(p.kind)) shape[k] = Shape{0, 0, 0, 0, 0};
+        else {
+            if (!fit(p.kind, gsz, shape[k], n)) return false;
+            lds = std::max(lds, res_lds_bytes(shape[k], C.W, HN));
+        }
+        used_max = std::max(used_max, n);
+    }
+    for (size_t k = 0; k < plans.size(); ++k)
+        if (!plans[k].latency && plans[k].count > 0) nwg[k] = used_max;
+    for (size_t k = 0; k < plans.size(); ++k)
+        if (plans[k].lead_kind < 0) lead_shape[k] = shape[k];
+    return true;
+}
+
 // Runs one single-design engine launch with descriptor D (already uploaded).
 // cm: the coarse mesh of a launch with coarse-mesh lanes (else nullptr).
 int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &plans, void *ws,
@@ -816,80 +969,17 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     const int sweep_wgs_res =
         T.sweep_wgs > 0 ? T.sweep_wgs : long_sweep ? std::min(64, std::max(40, C.Nn / 1000)) : 40;
 
-    const int NT = kThreads;
-    const int res_npt_max = T.resident_npt_max;
-    const int g_min = (C.Nn + NT * res_npt_max - 1) / (NT * res_npt_max);
-    bool resident = T.resident != 0 && g_min <= grid / 4 &&
-                    (C.Nn + g_min - 1) / g_min >= H && !C.gmg && !C.ckpt;
-    // a tile must be at least one halo (H nodes) long
-    const int max_wg_per_lane = std::max(1, C.Nn / H);
-
-    std::vector<int> ngroups(plans.size()), per_group(plans.size()), nwg(plans.size()),
-        tile(plans.size());
-    if (resident) {
-        // one tile of <= NT*npt nodes per workgroup; every group holds a whole lane
-        int lat_wgs = 0;
-        int nq = 0;
-        for (size_t k = 0; k < plans.size(); ++k) {
-            auto &p = plans[k];
-            if (p.latency) {
-                nwg[k] = p.fixed_nwg > 0 ? std::max(g_min, p.fixed_nwg)
-                                         : std::max(g_min, std::min(sweep_wgs_res, grid / 4));
-                nwg[k] = std::max(1, std::min(nwg[k], max_wg_per_lane));
-                ngroups[k] = p.count;
-                lat_wgs += nwg[k] * p.count;
-            } else {
-                nwg[k] = g_min;
-                ++nq;
-            }
-        }
-        const int avail = (grid - lat_wgs) / g_min;  // groups left for batched lanes
-        if (avail < nq) resident = false;
-        // without a sequential sweep (G = 0) the lanes are the whole pass:
-        // resident groups that cannot hold every lane at once leave the
-        // streaming form (all lanes at once, HBM-bound) ahead
-        int lanes = 0;
-        for (const auto &p : plans) lanes += p.latency ? 0 : p.count;
-        if (lat_wgs == 0 && avail < lanes && T.resident != 1) resident = false;
-    }
-    if (resident) {
-        int nq = 0;
-        double wF = 0.0;
-        int lat_wgs = 0;
-        for (size_t k = 0; k < plans.size(); ++k) {
-            if (plans[k].latency) lat_wgs += nwg[k] * plans[k].count;
-            else {
-                wF += plans[k].weight * plans[k].count;
-                ++nq;
-            }
-        }
-        const int avail = (grid - lat_wgs) / g_min;
-        int left = avail;
-        for (size_t k = 0; k < plans.size(); ++k) {
-            auto &p = plans[k];
-            if (p.latency) continue;
-            --nq;
-            int q = p.queues > 0 ? p.queues : (int)floor(avail * p.weight * p.count / wF);
-            q = std::max(1, std::min(q, std::min(p.count, left - nq)));
-            ngroups[k] = q;
-            left -= q;
-        }
-        // few batched lanes (e.g. one slice): spread each over more workgroups
-        int used_b = 0;
+    std::vector<int> ngroups(plans.size()), per_group(plans.size()), nwg(plans.size());
+    std::vector<Shape> shape(plans.size()), lead_shape(plans.size());
+    size_t res_lds = 0;
+    // checkpointed and multigrid lanes stream
+    bool resident = T.resident != 0 && !C.gmg && !C.ckpt;
+    if (resident)
+        resident = plan_resident(C, plans, T, grid, lds_cap_d, sweep_wgs_res, cm, ngroups, nwg,
+                                 shape, lead_shape, res_lds);
+    if (resident)
         for (size_t k = 0; k < plans.size(); ++k)
-            if (!plans[k].latency) used_b += ngroups[k] * g_min;
-        const int spread = std::max(1, (grid - lat_wgs) / std::max(used_b, 1));
-        for (size_t k = 0; k < plans.size(); ++k)
-            if (!plans[k].latency)
-                nwg[k] = std::max(g_min, std::min(g_min * spread, max_wg_per_lane));
-        for (size_t k = 0; k < plans.size(); ++k) {
-            per_group[k] = (plans[k].count + ngroups[k] - 1) / ngroups[k];
-            const int ts = (C.Nn + nwg[k] - 1) / nwg[k];
-            nwg[k] = (C.Nn + ts - 1) / ts;  // every workgroup owns a non-empty tile
-            if (ts < H || ts > NT * res_npt_max) return PT_EINVAL;
-            tile[k] = ts;
-        }
-    }
+            per_group[k] = ngroups[k] > 0 ? (plans[k].count + ngroups[k] - 1) / ngroups[k] : 0;
     if (!resident) {
         // streaming: explicit shapes first (sweeps, fixed fine lanes), then the
         // other lanes share the rest of the grid by weight, with at least
@@ -967,7 +1057,8 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
         }
         for (size_t k = 0; k < plans.size(); ++k) {
             per_group[k] = (plans[k].count + ngroups[k] - 1) / ngroups[k];
-            tile[k] = tile_for(C.Nn, nwg[k], H, lds_cap_d, T.tile_max);
+            shape[k] = Shape{tile_for(C.Nn, nwg[k], H, lds_cap_d, T.tile_max), 0, 0, 0, 0};
+            lead_shape[k] = shape[k];
         }
     }
     int used = 0, max_tile = 256, total_groups = 0;
@@ -975,20 +1066,15 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
         if (nwg[k] > kMaxGroup) return PT_EINVAL;
         used += nwg[k] * ngroups[k];
         total_groups += ngroups[k];
-        max_tile = std::max(max_tile, tile[k]);
+        max_tile = std::max(max_tile, shape[k].tile);
     }
     if (total_groups > Lay.s.max_groups) return PT_EINVAL;
     if (used > grid) grid = used;
     if (grid > kMaxGrid) return PT_EINVAL;
-    int npt = 0;
-    if (resident) {
-        npt = 1;
-        while (npt * NT < max_tile) npt *= 2;
-        if (cm || timed) npt = 8;  // the one resident form of these launches
-    }
     if (C.gmg && (C.gmg_chunk < 256 || C.gmg_chunk_init < 256)) return PT_EINVAL;
     size_t lds_bytes =
-        C.gmg ? gmg_lds_bytes(C) : engine_lds_doubles(max_tile, C.W) * sizeof(double);
+        resident ? res_lds
+                 : C.gmg ? gmg_lds_bytes(C) : engine_lds_doubles(max_tile, C.W) * sizeof(double);
     if (cm) {
         // a coarse-mesh lane stages two windows of its coarse tile and halo
         for (size_t k = 0; k < plans.size(); ++k)
@@ -1012,8 +1098,7 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
             else if (qb < 0) qb = (int)k;
             else qa = qb = -2;
         }
-        if (qa >= 0 && qb >= 0 &&
-            (nwg[qa] != nwg[qb] || tile[qa] != tile[qb] || plans[qa].dir != plans[qb].dir))
+        if (qa >= 0 && qb >= 0 && (nwg[qa] != nwg[qb] || plans[qa].dir != plans[qb].dir))
             qa = qb = -1;
         if (qb < 0) qa = qb = -1;
     }
@@ -1021,7 +1106,8 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
         QueueArgs &Q = P.Q;
         Q.ngroups = ngroups[qa] + ngroups[qb];
         Q.nwg = nwg[qa];
-        Q.tile = tile[qa];
+        Q.shapeA = shape[qa];
+        Q.shapeB = shape[qb];
         Q.kindA = plans[qa].kind;
         Q.nA = plans[qa].count;
         Q.sA0 = plans[qa].slice0;
@@ -1043,7 +1129,8 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
         R.kind = p.kind;
         R.ngroups = ngroups[k];
         R.nwg = nwg[k];
-        R.tile = tile[k];
+        R.shape = shape[k];
+        R.lead_shape = lead_shape[k];
         R.s0 = p.slice0;
         R.gstride = p.dir;                 // neighbouring groups take consecutive slices
         R.lstride = p.dir * ngroups[k];    // a group's queue advances by the group count
@@ -1058,8 +1145,8 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     PT_TRY(launch_check());
     PT_TRY(reset_launch_state(ws, Lay.s, 1, stream));
     const Launch X = make_launch(ws, Lay.s, ctl, C.timeout_ticks);
-    return launch_engine(C.fp32 != 0, npt, D, &E, X, grid, lds_bytes, dev, stream, cm != nullptr,
-                         timed);
+    const Engine K{resident, C.fp32 != 0, false, cm != nullptr, timed};
+    return launch_engine(K, D, &E, X, grid, lds_bytes, dev, stream);
 }
 
 // Fine lanes of a single-design pass. With checkpoints (or PT_FINE_WGS set)
@@ -1116,10 +1203,10 @@ __global__ void k_build_lanes(const EngineDesc *__restrict__ D, Lane *lanes) {
     const bool gk = E.I.gk_lanes != 0;
     int k = P.q0_lane0;
     auto put = [&](int pos, int kind, int slice, int tile) {
-        lanes[pos].kind = kind;
-        lanes[pos].slice = slice;
-        lanes[pos].design = d;
-        lanes[pos].tile = tile;
+        const int *v = kind == F_PRI || kind == F_ADJ     ? P.fine
+                       : kind == GK_PRI || kind == GK_ADJ ? P.gk
+                                                          : P.sweep;
+        put_lane(lanes + pos, kind, slice, d, Shape{tile, v[0], v[1], v[2], v[3]});
     };
     if (!P.adjoint) {
         for (int n = 0; n < Ntau; ++n) {
@@ -1190,6 +1277,21 @@ bool valid_tuning(const pt_batch_tuning *t) {
            (t->tile_max == 0 || (t->tile_max >= 256 && t->tile_max <= 16384));
 }
 
+constexpr int kBatchDegFine = 3, kBatchDegCoarse = 4;
+
+// tw, th, deg, nr of a design's resident lanes on groups of `wgs` workgroups.
+bool batch_shape(const Consts &C, int wgs, int deg, int lds_cap_d, int (&out)[4]) {
+    Shape s{};
+    int n = 0;
+    if (!res_shape(C.W, C.ny + 1, wgs, deg, kResRows, (size_t)lds_cap_d * sizeof(double), s, n))
+        return false;
+    out[0] = s.tw;
+    out[1] = s.th;
+    out[2] = s.deg;
+    out[3] = s.nr;
+    return true;
+}
+
 // Plans and runs one multi-design engine launch. `hd` holds the designs'
 // descriptors (C, B, I set); their DesignPlan is filled here and the
 // descriptors are uploaded.
@@ -1199,10 +1301,10 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
     Device dev;
     PT_TRY(device_info(dev));
     const bool fp32 = hd[0].C.fp32 != 0;
-    const int npt = T.resident ? 8 : 0;
     const int cap_d = lds_cap_doubles(dev);
+    bool resident = T.resident != 0;
     // tiles and LDS of every design on both kinds of worker
-    size_t lds_d = 0;
+    size_t lds_d = 0, res_lds = 0;
     for (auto &E : hd) {
         const Consts &C = E.C;
         const int H = C.W + 1;
@@ -1211,23 +1313,35 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
         if (T.resident) {
             t0 = (C.Nn + T.fine_wgs - 1) / T.fine_wgs;
             t1 = (C.Nn + T.sweep_wgs - 1) / T.sweep_wgs;
-            if (t0 < H || t1 < H || t0 > kThreads * npt || t1 > kThreads * npt) return PT_EINVAL;
+            const int most = kThreads * 8;
+            if (t0 < H || t1 < H || t0 > most || t1 > most) return PT_EINVAL;
             // every workgroup of a resident group owns a non-empty tile
             if ((C.Nn + t0 - 1) / t0 != T.fine_wgs || (C.Nn + t1 - 1) / t1 != T.sweep_wgs)
                 return PT_EINVAL;
-        } else {
-            t0 = tile_for(C.Nn, T.fine_wgs, H, cap_d, T.tile_max);
-            t1 = tile_for(C.Nn, T.sweep_wgs, H, cap_d, T.tile_max);
         }
+        t0 = tile_for(C.Nn, T.fine_wgs, H, cap_d, T.tile_max);
+        t1 = tile_for(C.Nn, T.sweep_wgs, H, cap_d, T.tile_max);
         E.plan.tile0 = t0;
         E.plan.tile1 = t1;
+        if (resident) {
+            // a design whose windows do not fit sends the batch to streaming groups
+            auto &f = E.plan.fine, &g = E.plan.gk, &s = E.plan.sweep;
+            resident = batch_shape(C, T.fine_wgs, kBatchDegFine, cap_d, f) &&
+                       batch_shape(C, T.fine_wgs, kBatchDegCoarse, cap_d, g) &&
+                       batch_shape(C, T.sweep_wgs, kBatchDegCoarse, cap_d, s);
+            for (const auto *v : {(const int *)f, (const int *)g, (const int *)s})
+                if (resident)
+                    res_lds = std::max(res_lds, res_lds_bytes(Shape{0, v[0], v[1], v[2], v[3]},
+                                                              C.W, C.ny + 1));
+        }
         E.plan.adjoint = adjoint ? 1 : 0;
         if (C.gmg && (C.gmg_chunk < 256 || C.gmg_chunk_init < 256)) return PT_EINVAL;
         lds_d = std::max(lds_d, C.gmg ? (gmg_lds_bytes(C) + 7) / 8
                                       : engine_lds_doubles(std::max(t0, t1), C.W));
     }
-    const size_t lds_bytes = lds_d * sizeof(double);
+    const size_t lds_bytes = resident ? res_lds : lds_d * sizeof(double);
     if (lds_bytes > (size_t)dev.lds_max) return PT_EINVAL;
+    const Engine K{resident, fp32, true, false, false};
     // designs with the longest sweeps first (N_tau solves of N_n nodes)
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);
@@ -1252,7 +1366,7 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
     }
     if (q0 + q1 > Lay.s.max_lanes) return PT_EINVAL;
     int cap = 0;
-    PT_TRY(engine_capacity(fp32, npt, true, lds_bytes, dev, cap));
+    PT_TRY(engine_capacity(K, lds_bytes, dev, cap));
     int grid = std::min(cap, kMaxGrid);
     if (T.grid > 0) grid = std::min(grid, T.grid);
     GroupArgs A{};
@@ -1276,7 +1390,7 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
     PT_TRY(launch_check());
     PT_TRY(reset_launch_state(ws, Lay.s, n, stream));
     const Launch X = make_launch(ws, Lay.s, hd[0].B.ctl, hd[0].C.timeout_ticks);
-    return launch_engine(fp32, npt, D, nullptr, X, A.grid, lds_bytes, dev, stream);
+    return launch_engine(K, D, nullptr, X, A.grid, lds_bytes, dev, stream);
 }
 
 bool valid_batch(int n, const pt_problem *probs) {

@@ -50,7 +50,10 @@ struct Lane {
     int kind;
     int slice;      // n for F/GK lanes; unused for sweeps
     int design;     // index into the launch's design descriptors
-    int tile;       // nodes per workgroup tile for this lane on its group
+    int tile;       // nodes per workgroup tile for this lane on its group (streaming)
+    // resident lanes: nodes of a workgroup's rectangle, degree of the
+    // preconditioner's polynomial, window rows per thread
+    int tw, th, deg, nr;
 };
 
 // A group of workgroups runs a queue of lanes one after another; its
@@ -86,6 +89,8 @@ struct Control {
     int epoch;
     int pad1;
     double grad_scale;  // factor of the summed sensitivities: Theta^{1-p}/p with G = 0, else 1
+    // smallest and largest (k/6) / (c hx hy/36) of an element, as double bits
+    unsigned long long kmin_bits, kmax_bits;
 };
 
 struct Consts {
@@ -193,6 +198,7 @@ struct DesignPlan {
     int q1_cold, q1_sweep;   // lane index of the cold / correction sweep (-1: none)
     int tile0, tile1;        // tile of this design's lanes on queue 0 / queue 1 groups
     int adjoint;             // lane kinds of the adjoint pass
+    int fine[4], gk[4], sweep[4];  // resident lanes: tw, th, deg, nr
 };
 
 // Coarse-spatial-mesh propagators (propagator PT_COARSE_MESH): the coarse
@@ -224,8 +230,6 @@ struct Launch {
     const Lane *lanes;     // [n_lanes]
     unsigned *bar;         // [kMaxGroups][kBarParts][kBarLine] group barrier counters
     double *partials;      // [kMaxGroups][2][kMaxGroup][4]
-    double *xch;           // resident-mode halo exchange [grid][2][2][3][xch_stride]
-    int xch_stride;        // >= W + 1 of every design
     unsigned *qhead;       // [2] next untaken position of each shared queue
     int *qslot;            // [kMaxGroups] lane position a group leader took
     unsigned long long *trace;  // per-lane record [n_lanes][trace_stride]
