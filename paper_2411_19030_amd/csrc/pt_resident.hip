@@ -6,7 +6,7 @@
 // and Gear with a polynomial preconditioner: u = q(D^{-1}A) D^{-1} r, the result
 // of d + 1 Richardson sweeps z += omega_i D^{-1} (r - A z) from z = 0 whose
 // omega_i are the inverse roots of the Chebyshev polynomial of degree d + 1 on
-// an interval inside the spectrum's bounds (res_omegas). A round of a group is
+// an interval inside the spectrum's bounds (res_omega). A round of a group is
 // bound by latency, not by arithmetic: the barrier, the partial sums and the
 // halo each cost a trip through the memory side of the chip, about 4 us
 // together, while one application of the operator to a tile costs about half a
@@ -40,9 +40,9 @@
 // it, lowers the order where the states are not smooth.
 //
 // Measured at 256^2, 512 steps in 32 slices, cg_rtol 1e-12, one warm cycle,
-// against Jacobi CG on full-row tiles with one halo row: 94 -> 31.5 ms; CG
+// against Jacobi CG on full-row tiles with one halo row: 94 -> 29.5 ms; CG
 // rounds per fine step 42 -> 8 (degree 3, extrapolated), per coarse step 169 ->
-// 36 (degree 4); sequential 100^2 with 480 steps: 741 -> 131 ms.
+// 36 (degree 4); sequential 100^2 with 480 steps: 741 -> 120 ms.
 
 namespace pt {
 
@@ -202,6 +202,608 @@ struct ResTimers {
     long long mark = 0;
 };
 
+constexpr int kRim = 2;  // rim cells per thread
+
+// What one thread holds of its workgroup's window: its column gx, rows gy0 ..
+// gy0 + NR - 1, and the node sets as bits per row: live (in the grid, the window
+// and not fixed), fill (the same with one row more above the window), own, nodes
+// that a neighbour's window (edge) or set-up window (edge1: one ring more) holds.
+// The rim are the cells around the window that no thread's rows cover (id -1: no
+// node there).
+struct ResGeo {
+    int W, gx, gy0;
+    int cell0;     // LDS cell of the row below the first node
+    int sz, zlen;  // row length and length of an operand window
+    unsigned live, fill, own, edge, edge1;
+    int rim_id[kRim], rim_cell[kRim];
+    bool act;
+
+    __device__ __forceinline__ unsigned id(int k) const {
+        return (unsigned)(fresh(gy0 * W + gx) + k * W);
+    }
+    static __device__ __forceinline__ bool is(unsigned m, int k) {
+        return (((unsigned)fresh((int)m) >> k) & 1u) != 0;
+    }
+    // this thread's slots of p, then of x
+    template <int NR>
+    __device__ __forceinline__ int slot_p() const { return 2 * zlen + (int)threadIdx.x; }
+    template <int NR>
+    __device__ __forceinline__ int slot_x() const {
+        return 2 * zlen + NR * kThreads + (int)threadIdx.x;
+    }
+    // A row of global values at the thread's nodes in m, all loads in flight at
+    // once: no load is conditional (the other nodes read node 0), since a masked
+    // load whose value is used in its own branch waits for it there, node by node.
+    template <int NR>
+    __device__ __forceinline__ void load(const double *row, unsigned m, double (&v)[NR]) const {
+#pragma unroll
+        for (int k = 0; k < NR; ++k) v[k] = ldg(row, is(m, k) ? id(k) : 0u);
+    }
+    __device__ __forceinline__ void load_rim(const double *row, double (&v)[kRim]) const {
+#pragma unroll
+        for (int i = 0; i < kRim; ++i) v[i] = ldg(row, rim_id[i] >= 0 ? (unsigned)rim_id[i] : 0u);
+    }
+    template <int NR>
+    __device__ __forceinline__ void store(const double *row, unsigned m,
+                                          const double (&v)[NR]) const {
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            if (is(m, k)) *nd(row, id(k)) = v[k];
+    }
+    // the operand window at LDS index zb
+    template <int NR>
+    __device__ __forceinline__ void put(int zb, const double (&v)[NR],
+                                        const double (&vr)[kRim]) const {
+        extern __shared__ double lds[];
+        if (act) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) lds[zb + cell0 + (k + 1) * sz] = is(fill, k) ? v[k] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < kRim; ++i)
+            if (rim_id[i] >= 0) lds[zb + rim_cell[i]] = vr[i];
+    }
+    // The operator at the thread's nodes from the element values: gap k lies below
+    // row k, its elements left and right of the column are (gx - 1, gy0 + k - 1) and
+    // (gx, gy0 + k - 1); cc is the diagonal.
+    template <int NR>
+    __device__ __forceinline__ void coefs(const Consts &C, const Bufs &B, bool fine,
+                                          ResCoef<NR> &Q, double (&cc)[NR]) const {
+        const double ms = fine ? C.inv_dt : C.inv_dtau;
+        const bool inx = act && gx >= 0 && gx < W;
+        double ml[NR + 1], mr[NR + 1], kl[NR + 1], kr[NR + 1];
+#pragma unroll
+        for (int k = 0; k <= NR; ++k) {
+            const int ey = gy0 + k;  // padded element row
+            const bool in = inx && ey >= 0 && ey <= C.ny + 1;
+            // (element 0 is padding: its values are 0)
+            const unsigned e = in ? (unsigned)(ey * C.EW + gx) : 0u, d = in ? 1u : 0u;
+            ml[k] = *nd(B.cm, e);
+            mr[k] = *nd(B.cm, e + d);
+            kl[k] = *nd(B.kq, e);
+            kr[k] = *nd(B.kq, e + d);
+        }
+        double sl = 0.0, sr = 0.0, xl = 0.0, xr = 0.0;
+#pragma unroll
+        for (int k = 0; k <= NR; ++k) {
+            const double a = ml[k] * ms, b = mr[k] * ms;
+            Q.dl[k] = a + C.e_d * kl[k];
+            Q.dr[k] = b + C.e_d * kr[k];
+            Q.nn[k] = 2.0 * (a + b) + C.e_y * (kl[k] + kr[k]);
+            const double nsl = 4.0 * a + C.e_self * kl[k], nsr = 4.0 * b + C.e_self * kr[k];
+            const double nxl = 2.0 * a + C.e_x * kl[k], nxr = 2.0 * b + C.e_x * kr[k];
+            if (k > 0) {
+                Q.el[k - 1] = xl + nxl;
+                Q.er[k - 1] = xr + nxr;
+                cc[k - 1] = (sl + sr) + (nsl + nsr);
+            }
+            sl = nsl;
+            sr = nsr;
+            xl = nxl;
+            xr = nxr;
+        }
+    }
+};
+
+// A lane as its set-up, restart and commit phases see it. The rounds of CG are a loop
+// of their own behind these phases: as one loop over phases the allocator put parts of
+// the operator, which the rounds read, into scratch for the set-up's sake. Solve of 8
+// rounds, set-up included, 257x257 nodes on 63 workgroups (NR 6): 13.6 -> 11.4 us a
+// round; 101x101 on 40 (NR 2, no spill left): 7.1 -> 5.8 us.
+struct ResLaneCtx {
+    const EngineDesc *D;
+    const double *gv0;  // group vectors from R0 on, gvs apart
+    size_t gvs;
+    unsigned long long *trec;
+    int kind, slice, trace_steps;
+    bool trunc, leader;
+    int step, nsteps;  // the solve last set up (1..nsteps), solves of the lane
+    int sp_n, sp_j, sp_jprev, st_n, st_j, st_jprev;  // of that solve, of the next one
+    int order, ext_cap;  // extrapolation of the next solve's start; its cap
+    // theta carried by the lane; on fine lanes its p-th power, whose root is taken
+    // once at the end (with G = 0: the slice's part of Theta~)
+    double theta, src_scale;
+    // residual of the finished solve, ||x||_p^p, ||b||^2, ||r0||^2, two sums of the
+    // round, and the plain start's ||r0||^2 (this thread's parts)
+    double sum[7];
+};
+
+// group vectors by consecutive pool slots, so that a choice between them is
+// arithmetic on one base: w by round parity; right-hand sides of the solve being
+// finished and of the next one (each value read by its writer only); the last
+// four solutions
+__device__ __forceinline__ const double *res_w(const double *gv0, size_t gvs, unsigned par) {
+    return gv0 + (size_t)(V_W0 - V_R0 + (par & 1)) * gvs;
+}
+__device__ __forceinline__ const double *res_b(const double *gv0, size_t gvs, int j) {
+    return gv0 + (size_t)(j & 1) * gvs;
+}
+__device__ __forceinline__ const double *res_x(const double *gv0, size_t gvs, int j) {
+    return gv0 + (size_t)(V_S0 - V_R0 + (j & 3)) * gvs;
+}
+
+// The set-up: true residual and outputs of the finished solve
+// (ctx.step > 0), then right-hand side, start and residual of the next one. The
+// residual r0 of the thread's nodes is left in their cells of window 1. Returns
+// false when a wait timed out or another workgroup aborted.
+template <int NR>
+__device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, const ResCoef<NR> &A,
+                                          const double (&cc)[NR]) {
+    extern __shared__ double lds[];
+    const ResGeo g = geo;
+    auto is = [](unsigned m, int k) { return ResGeo::is(m, k); };
+    const EngineDesc *Dp = x.D;
+    const Consts C = fetch(&Dp->C);
+    const Bufs B = fetch(&Dp->B);
+    const LaunchInfo I = fetch(&Dp->I);
+    Control *ctl = B.ctl;
+    const long long tmo = C.timeout_ticks;
+    Lane L;
+    L.kind = x.kind;
+    L.slice = x.slice;
+    const int step = x.step, nsteps = x.nsteps;
+    const bool trunc = x.trunc;
+    const bool is_adj = is_adjoint_kind(L.kind);
+    const bool sweep = L.kind == SWEEP_PRI || L.kind == SWEEP_ADJ;
+    const bool fine = L.kind == F_PRI || L.kind == F_ADJ;
+    const bool prev = step > 0, next = step < nsteps, last = prev && !next;
+    const int sp_n = x.sp_n, sp_j = x.sp_j, sp_jprev = x.sp_jprev;
+    const double *gv0 = x.gv0;
+    const size_t gvs = x.gvs;
+    auto xh = [&](int j) { return res_x(gv0, gvs, j); };
+    // x of solve `step` is kept in history slot `step` once it is finished
+    const double *xp = xh(step);
+    const size_t Nn = C.Nn;
+    const int sz = g.sz, zlen = g.zlen, cell0 = g.cell0, W = g.W, HN = C.ny + 1;
+    const int LP = g.slot_p<NR>(), LX = g.slot_x<NR>();
+    double sum[7] = {0, 0, 0, 0, 0, 0, 0};
+
+    StepInfo st{};
+    if (next) {
+        st = step_info(C, B, I, L, step, xp);
+        x.st_n = st.n;
+        x.st_j = st.j;
+        x.st_jprev = st.jprev;
+    }
+    // waits: the guess of a cold-started slice; what a sweep's step reads
+    auto waitf = [&](int idx) { return wait_flag(B.flags, idx, I.epoch, ctl, tmo); };
+    if (next && st.wait) {
+        if (!waitf(st.wait_idx)) return false;
+        if (L.kind == F_PRI && I.cold && L.slice > 0)
+            x.theta = ipow(ldc(B.Gk_th + L.slice - 1), C.p);
+    }
+    if (sweep) {
+        if (step == 0) {
+            if (!waitf(flag_index(FL_F, L.kind == SWEEP_PRI ? 0 : C.Ntau))) return false;
+            if (L.kind == SWEEP_PRI) x.theta = ldc(B.F_th);
+        } else if (!waitf(flag_index(FL_F, sp_n))) {
+            return false;
+        }
+        if (next && (I.cold || I.gk_lanes))
+            if (!waitf(flag_index(I.cold ? FL_COLD : FL_GK, st.n))) return false;
+    }
+    const bool terms = L.kind == F_ADJ || L.kind == SWEEP_ADJ;
+    // window 0: x of the finished solve, window 1: the operand tp of the next
+    // right-hand side where it is another vector (a sweep's next input
+    // u = x + F_n - G(u^k_n), a lane's first input)
+    double zc[NR], t[NR], v[NR], bv[NR], vr[kRim], br[kRim];
+    // states of the slice before this one extrapolate; differences that reach back
+    // to the slice's given first state, which may be off in its rough modes, are
+    // not used
+    int order = 0;
+    if (fine && next && C.extrap) order = step >= 2 ? 1 : 0;
+    else if (fine && next && prev) order = max(0, min(min(step - 2, 3), x.ext_cap));
+    x.order = order;
+    // x0 = ca x + h, h the older states' part: loaded here with the others, so that
+    // the round pays for one memory latency instead of one a state
+    const double ca = (double)(order + 1);
+    double h[NR], hr[kRim];
+    if (order > 0) {
+        g.load<NR>(xh(step - 1), g.fill, h);
+        g.load_rim(xh(step - 1), hr);
+        const double cb = order == 1 ? -1.0 : order == 2 ? -3.0 : -6.0;
+        if (order > 1) {
+            double a[NR], ar[kRim], a3[NR], a3r[kRim];
+            // (a third state that the order does not use is read all the same)
+            g.load<NR>(xh(step - 2), g.fill, a);
+            g.load_rim(xh(step - 2), ar);
+            g.load<NR>(xh(step - 3), g.fill, a3);
+            g.load_rim(xh(step - 3), a3r);
+            const double cd = order == 2 ? 1.0 : 4.0;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) h[k] = cb * h[k] + cd * a[k] - (order > 2 ? a3[k] : 0.0);
+#pragma unroll
+            for (int i = 0; i < kRim; ++i)
+                hr[i] = cb * hr[i] + cd * ar[i] - (order > 2 ? a3r[i] : 0.0);
+        } else {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) h[k] = cb * h[k];
+#pragma unroll
+            for (int i = 0; i < kRim; ++i) hr[i] = cb * hr[i];
+        }
+    }
+    if (prev) {
+        // own values of x from the thread's slots, the others as published
+        g.load<NR>(xp, g.fill & ~g.own, v);
+        g.load_rim(xp, vr);
+        if (!terms) g.load<NR>(res_b(gv0, gvs, step), g.own & g.live, bv);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) v[k] = is(g.own, k) ? lds[LX + k * kThreads] : v[k];
+        if (sweep) {
+            const double *Fp = L.kind == SWEEP_PRI ? B.S + (size_t)(C.M * (sp_n + 1) - 1) * Nn
+                                                   : B.FL + (size_t)sp_n * Nn;
+            const double *Gp = B.Gk + (size_t)sp_n * Nn;
+            double fr[kRim], gr[kRim];
+            g.load<NR>(Fp, g.fill, zc);
+            g.load<NR>(Gp, g.fill, t);
+            g.load_rim(Fp, fr);
+            g.load_rim(Gp, gr);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) zc[k] = v[k] + (zc[k] - t[k]);
+#pragma unroll
+            for (int i = 0; i < kRim; ++i) br[i] = vr[i] + (fr[i] - gr[i]);
+            g.put<NR>(zlen, zc, br);
+        }
+        g.put<NR>(0, v, vr);
+    } else {
+        g.load<NR>(st.tp_src, g.fill, v);
+        g.load_rim(st.tp_src, vr);
+        g.put<NR>(zlen, v, vr);
+#pragma unroll
+        for (int i = 0; i < kRim; ++i) br[i] = vr[i];
+    }
+    lds_sync();
+    if (prev && terms) {
+        // terms of the elements right above the owned nodes; they wait in p's
+        // slots until the residual has been accepted
+        const double *Tr = B.S + (size_t)(sp_j - 1) * Nn;
+        const double *Tp = sp_jprev > 0 ? B.S + (size_t)(sp_jprev - 1) * Nn : nullptr;
+        const double *Gp = B.Gk + (size_t)sp_n * Nn;
+        const double idl = fine ? C.inv_dt : C.inv_dtau;
+        auto corner = [&](const double *row, int k, int dx) {
+            const int y = g.gy0 + k;
+            const bool in = g.act && g.gx >= 0 && g.gx + dx < W && y >= 0 && y < HN;
+            return *nd(row, in ? (unsigned)(y * W + g.gx + dx) : 0u);
+        };
+        double ta[NR + 1], tb[NR + 1], pa[NR + 1], pb[NR + 1], dk[NR], dc[NR];
+        unsigned e[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int y = g.gy0 + k;
+            const bool el = is(g.own, k) && g.gx < C.nx && y < C.ny;
+            e[k] = el ? (unsigned)(y * C.nx + g.gx) : 0u;
+            dk[k] = *nd(B.dk, e[k]);
+        }
+#pragma unroll
+        for (int k = 0; k <= NR; ++k) {
+            ta[k] = corner(Tr, k, 0);
+            tb[k] = corner(Tr, k, 1);
+        }
+        if (I.has_dc) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) dc[k] = *nd(B.dc, e[k]);
+#pragma unroll
+            for (int k = 0; k <= NR; ++k) {
+                pa[k] = Tp ? corner(Tp, k, 0) : 0.0;
+                pb[k] = Tp ? corner(Tp, k, 1) : 0.0;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int z = cell0 + (k + 1) * sz;
+            double l0 = lds[z], l1 = lds[z + 1], l2 = lds[z + sz + 1], l3 = lds[z + sz];
+            if (sweep) {
+                const int y = g.gy0 + k;
+                const bool el = is(g.own, k) && g.gx < C.nx && y < C.ny;
+                const unsigned id = el ? (unsigned)(y * W + g.gx) : 0u;
+                const unsigned up = el ? id + W : 0u, dx = el ? 1u : 0u;
+                l0 -= ldg(Gp, id);
+                l1 -= ldg(Gp, id + dx);
+                l2 -= ldg(Gp, up + dx);
+                l3 -= ldg(Gp, up);
+            }
+            double term = dk[k] * elem_k(C, l0, l1, l2, l3, ta[k], tb[k], tb[k + 1], ta[k + 1]);
+            if (I.has_dc)
+                term += dc[k] * idl *
+                        elem_c(C, l0, l1, l2, l3, ta[k] - pa[k], tb[k] - pb[k],
+                               tb[k + 1] - pb[k + 1], ta[k + 1] - pa[k + 1]);
+            lds[LP + k * kThreads] = term;
+        }
+    }
+    if (prev) {
+        // ---- the finished solve: true residual, norm -----------------------------
+        if (terms) g.load<NR>(res_b(gv0, gvs, step), g.own & g.live, bv);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) bv[k] = is(g.own & g.live, k) ? bv[k] : 0.0;
+        res_apply<NR>(A, cell0, sz, bv, zc, t);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const double rv = is(g.live & g.own, k) ? t[k] - cc[k] * zc[k] : 0.0;
+            sum[0] += rv * rv;
+        }
+        if (!is_adj) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) sum[1] += ipow(is(g.own, k) ? zc[k] : 0.0, C.p);
+        }
+    }
+    if (next) {
+        // ---- the next solve: b, x0, r0 --------------------------------------------
+        // source
+        if (st.adjoint) {
+            const double ss = x.src_scale;
+            g.load<NR>(B.S + (size_t)(st.j - 1) * Nn, g.live, bv);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) bv[k] = ss * ipow(bv[k], C.p - 1);
+        } else {
+            const double f = B.qt[st.j] * C.quarter_area * (double)((g.gx > 0) + (g.gx < C.nx));
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+                bv[k] = f * (double)((g.gy0 + k > 0) + (g.gy0 + k < C.ny));
+        }
+        {
+            // + (C/delta) tp on the window
+            const double ms = fine ? C.inv_dt : C.inv_dtau;
+            int z = (prev && !sweep ? 0 : zlen) + cell0;
+            double ml[NR + 1], mr[NR + 1];
+            if (I.has_dc) {
+                const bool inx = g.act && g.gx >= 0 && g.gx < W;
+#pragma unroll
+                for (int k = 0; k <= NR; ++k) {
+                    const int ey = g.gy0 + k;
+                    const bool in = inx && ey >= 0 && ey <= C.ny + 1;
+                    const unsigned e = in ? (unsigned)(ey * C.EW + g.gx) : 0u;
+                    ml[k] = *nd(B.cm, e) * ms;
+                    mr[k] = *nd(B.cm, e + (in ? 1u : 0u)) * ms;
+                }
+            } else {
+                // c is the same everywhere: no loads
+                const double m = *nd(B.cm, (unsigned)C.EW + 1u) * ms;
+#pragma unroll
+                for (int k = 0; k <= NR; ++k) {
+                    const bool in = g.gy0 + k >= 1 && g.gy0 + k <= C.ny;
+                    ml[k] = in && g.gx >= 1 ? m : 0.0;
+                    mr[k] = in && g.gx < C.nx ? m : 0.0;
+                }
+            }
+            double l0 = lds[z - 1], c0 = lds[z], r0 = lds[z + 1];
+            z += sz;
+            double l1 = lds[z - 1], c1 = lds[z], r1 = lds[z + 1];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                z += sz;
+                const double l2 = lds[z - 1], c2 = lds[z], r2 = lds[z + 1];
+                const double ml0 = ml[k], mr0 = mr[k], ml1 = ml[k + 1], mr1 = mr[k + 1];
+                double m = 4.0 * ((ml0 + mr0) + (ml1 + mr1)) * c1;
+                m += 2.0 * ((mr0 + mr1) * r1 + (ml0 + ml1) * l1 + (ml1 + mr1) * c2 +
+                            (ml0 + mr0) * c0);
+                m += mr1 * r2 + ml1 * l2 + mr0 * r0 + ml0 * l0;
+                bv[k] = is(g.live, k) ? m + bv[k] : 0.0;
+                l0 = l1;
+                c0 = c1;
+                r0 = r1;
+                l1 = l2;
+                c1 = c2;
+                r1 = r2;
+            }
+        }
+        if (order > 0) {
+            // residual of the plain start x0 = x: it judges the extrapolation
+            res_apply<NR>(A, cell0, sz, bv, zc, t);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                const double rv = is(g.live & g.own, k) ? t[k] - cc[k] * zc[k] : 0.0;
+                sum[6] += rv * rv;
+                v[k] = ca * zc[k] + h[k];
+            }
+            // (a row that only the set-up window holds has no node in zc's rows)
+#pragma unroll
+            for (int i = 0; i < kRim; ++i) vr[i] = ca * vr[i] + hr[i];
+        } else if (!prev || sweep) {
+            // x0 from the step's description; uc, br: its operand tp
+            double uc[NR];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) uc[k] = lds[zlen + cell0 + (k + 1) * sz];
+            if (trunc) {
+#pragma unroll
+                for (int k = 0; k < NR; ++k) v[k] = uc[k];
+#pragma unroll
+                for (int i = 0; i < kRim; ++i) vr[i] = br[i];
+            } else {
+                g.load<NR>(st.x0_src, g.fill, v);
+                g.load_rim(st.x0_src, vr);
+                if (st.d1) {
+                    double a[NR], ar[kRim];
+                    g.load<NR>(st.d0, g.fill, a);
+                    g.load_rim(st.d0, ar);
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) v[k] += uc[k] - a[k];
+#pragma unroll
+                    for (int i = 0; i < kRim; ++i) vr[i] += br[i] - ar[i];
+                }
+            }
+            if (!prev && sweep) {
+                // what the sweep publishes of its input
+                g.store<NR>(L.kind == SWEEP_PRI ? B.out_T + Nn
+                                                : B.out_L + (size_t)(C.Ntau - 1) * Nn,
+                            g.own, uc);
+                if (is_adj) {
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) uc[k] = 0.0;
+                    g.store<NR>(B.out_L + (size_t)C.Ntau * Nn, g.own, uc);
+                }
+            }
+        }
+        if (!prev || sweep || order > 0) {
+            lds_sync();
+            g.put<NR>(0, v, vr);
+            lds_sync();
+        }
+        res_apply<NR>(A, cell0, sz, bv, zc, t);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            t[k] = is(g.live, k) ? t[k] - cc[k] * zc[k] : 0.0;
+            const double bo = is(g.own, k) ? bv[k] : 0.0, ro = is(g.own, k) ? t[k] : 0.0;
+            sum[2] += bo * bo;
+            sum[3] += ro * ro;
+        }
+    }
+    if (prev) {
+        // the finished x to its outputs and the history, behind the round's loads: a
+        // load or a register reload issued after these stores would wait for them
+#pragma unroll
+        for (int k = 0; k < NR; ++k) v[k] = lds[LX + k * kThreads];
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            if (is(g.own, k)) stg(xp, g.id(k), v[k]);
+        if (L.kind == F_PRI) {
+            g.store<NR>(B.S + (size_t)(sp_j - 1) * Nn, g.own, v);
+            if (C.plt && last) g.store<NR>(B.out_T + (size_t)(L.slice + 1) * Nn, g.own, v);
+        } else if (L.kind == F_ADJ) {
+            if (last) g.store<NR>(B.FL + (size_t)L.slice * Nn, g.own, v);
+            if (C.plt && last) g.store<NR>(B.out_L + (size_t)(L.slice - 1) * Nn, g.own, v);
+        } else {
+            g.store<NR>((sweep ? B.Gn : B.Gk) + (size_t)sp_n * Nn, g.own, v);
+        }
+        if (sweep) {
+            // (the slice-end slot of S, still read as F_n by the neighbours in this
+            // round, follows after the barrier)
+            const double *row = L.kind == SWEEP_PRI ? B.out_T + (size_t)(sp_n + 1) * Nn
+                                                    : B.out_L + (size_t)(sp_n - 1) * Nn;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) v[k] = lds[zlen + cell0 + (k + 1) * sz];
+            g.store<NR>(row, g.own, v);
+        }
+    }
+    if (next) {
+        g.store<NR>(res_b(gv0, gvs, step + 1), g.own, bv);
+        // x of the new solve (the finished x is in the history)
+#pragma unroll
+        for (int k = 0; k < NR; ++k) lds[LX + k * kThreads] = zc[k];
+        lds_sync();  // both operand windows have been read
+        if (g.act) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) lds[zlen + cell0 + (k + 1) * sz] = t[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 7; ++k) x.sum[k] = sum[k];
+    return true;
+}
+
+// The true residual of the finished solve again, x taken back from the history:
+// left at the owned nodes' cells of window 1.
+template <int NR>
+__device__ __forceinline__ void res_residual(const ResGeo &geo, ResLaneCtx &x, const ResCoef<NR> &A,
+                                             const double (&cc)[NR]) {
+    extern __shared__ double lds[];
+    const ResGeo g = geo;
+    const EngineDesc *Dp = x.D;
+    const Consts C = fetch(&Dp->C);
+    const Bufs B = fetch(&Dp->B);
+    const int step = x.step, kind = x.kind;
+    const double *gv0 = x.gv0;
+    const size_t gvs = x.gvs;
+    const double *xp = res_x(gv0, gvs, step);
+    double zc[NR], t[NR], v[NR], vr[kRim];
+    g.load<NR>(xp, g.fill | g.own, v);
+    g.load_rim(xp, vr);
+    const int LX = g.slot_x<NR>();
+#pragma unroll
+    for (int k = 0; k < NR; ++k) lds[LX + k * kThreads] = v[k];
+    g.put<NR>(0, v, vr);
+    g.load<NR>(res_b(gv0, gvs, step), g.own & g.live, v);
+    lds_sync();
+    res_apply<NR>(A, g.cell0, g.sz, v, zc, t);
+    if (g.act) {
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            lds[g.zlen + g.cell0 + (k + 1) * g.sz] =
+                ResGeo::is(g.live & g.own, k) ? t[k] - cc[k] * zc[k] : 0.0;
+    }
+}
+
+// Books the finished solve after its residual has been accepted: sensitivity
+// sums, the corrected slice end, theta (pn: the group's ||x||_p^p), flags.
+template <int NR>
+__device__ __forceinline__ void res_commit(const ResGeo &geo, ResLaneCtx &x, double pn) {
+    extern __shared__ double lds[];
+    const ResGeo g = geo;
+    auto is = [](unsigned m, int k) { return ResGeo::is(m, k); };
+    const EngineDesc *Dp = x.D;
+    const Consts C = fetch(&Dp->C);
+    const Bufs B = fetch(&Dp->B);
+    const int kind = x.kind, slice = x.slice, step = x.step;
+    const int n = x.sp_n;
+    const bool fine = kind == F_PRI || kind == F_ADJ, last = step == x.nsteps;
+    const bool leader = x.leader;
+    if (kind == F_ADJ || kind == SWEEP_ADJ) {
+        const double *ac = fine ? B.acc + (size_t)(slice - 1) * C.Ne : B.accG;
+        const int LP = g.slot_p<NR>();
+        auto el = [&](int k) { return is(g.own, k) && g.gx < C.nx && g.gy0 + k < C.ny; };
+        auto eid = [&](int k) { return (unsigned)((g.gy0 + k) * C.nx + g.gx); };
+        double a[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) a[k] = step > 1 ? *nd(ac, el(k) ? eid(k) : 0u) : 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            if (el(k)) *nd(ac, eid(k)) = a[k] + lds[LP + k * kThreads];
+    }
+    if (kind == SWEEP_PRI) {
+        double u[NR];
+        const double *row = B.out_T + (size_t)(n + 1) * C.Nn;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) u[k] = *nd(row, is(g.own, k) ? g.id(k) : 0u);
+        g.store<NR>(B.S + (size_t)(C.M * (n + 1) - 1) * C.Nn, g.own, u);
+    }
+    if (!is_adjoint_kind(kind)) {
+        double theta = x.theta;
+        if (fine) {
+            theta += pn * C.inv_NtNe;
+            if (leader && last) B.F_th[slice] = C.plt ? theta : pow_call(theta, C.inv_p);
+        } else {
+            const double thG = pow_call(ipow(theta, C.p) + pn * C.inv_NtauNe, C.inv_p);
+            theta = thG;
+            if (kind == SWEEP_PRI) {
+                theta = thG + ldc(B.F_th + n) - ldc(B.Gk_th + n);
+                if (leader) {
+                    B.out_th[n + 1] = theta;
+                    B.Gn_th[n] = thG;
+                }
+            } else if (leader) {
+                B.Gk_th[n] = thG;
+            }
+        }
+        x.theta = theta;
+    }
+    if (leader) {
+        const unsigned epoch = fetch(&Dp->I).epoch;
+        if (kind == GK_PRI || kind == GK_ADJ) set_flag(B.flags, flag_index(FL_GK, n), epoch);
+        if (kind == COLD_PRI || kind == COLD_ADJ) set_flag(B.flags, flag_index(FL_COLD, n), epoch);
+        if (fine && last) set_flag(B.flags, flag_index(FL_F, slice), epoch);
+        if (step - 1 < x.trace_steps) x.trec[TR_HDR + step - 1] = (unsigned long long)now_ticks();
+    }
+}
+
 // Runs lane L of design *Dp on this workgroup's group (rank of g workgroups);
 // returns false when a wait timed out or another workgroup aborted, alike in
 // every workgroup.
@@ -216,144 +818,134 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
     const int tid = threadIdx.x;
     const bool leader = rank == 0 && tid == 0;
     const bool is_adj = is_adjoint_kind(L.kind);
-    const bool sweep = L.kind == SWEEP_PRI || L.kind == SWEEP_ADJ;
     const bool fine = L.kind == F_PRI || L.kind == F_ADJ;
-    const Consts C0 = fetch(&Dp->C);
-    const Bufs B0 = fetch(&Dp->B);
-    Control *ctl = B0.ctl;
-    const long long tmo = C0.timeout_ticks;
-    const int W = C0.W, HN = C0.ny + 1;
-    const double rtol = C0.rtol;
-    const int max_iter = C0.max_iter;
-    const int coarse_iters = fine ? 0 : C0.coarse_iters;
-    const bool trunc = coarse_iters > 0;
-    const int deg = trunc ? 0 : L.deg;
-    // group vectors by consecutive pool slots, so that a choice between them is
-    // arithmetic on one base: w by round parity; right-hand sides of the solve
-    // being finished and of the next one (each value read by its writer only);
-    // the last four solutions
-    const double *gv0 = group_vec(B0, G.vec, V_R0);
-    const size_t gvs = B0.pool_stride;
-    auto wv = [&](unsigned par) { return gv0 + (size_t)(V_W0 - V_R0 + (par & 1)) * gvs; };
-    auto bvec = [&](int j) { return gv0 + (size_t)(j & 1) * gvs; };
-    auto xh = [&](int j) { return gv0 + (size_t)(V_S0 - V_R0 + (j & 3)) * gvs; };
-
-    // geometry: owned rectangle, window, this thread's column and rows
-    const int TX = (W + L.tw - 1) / L.tw, TY = (HN + L.th - 1) / L.th;
-    const int hx = TX > 1 ? deg + 1 : 0, hy = TY > 1 ? deg + 1 : 0;
-    const int wc = L.tw + 2 * hx, wr = L.th + 2 * hy;
-    const int nq = min(kThreads / wc, (wr + NR - 1) / NR);
-    const int sz = wc + 2, rows = nq * NR;
-    const int zlen = sz * (rows + 2);   // doubles per operand window
-    double *LP = lds + 2 * zlen + tid;  // thread's p, then x
-    double *LX = LP + NR * kThreads;
-    const int q = tid / wc;
-    const bool act = q < nq;
-    const int col = act ? tid - q * wc : 0, row0 = act ? q * NR : 0;
-    const int cell0 = row0 * sz + col + 1;  // cell of the row below the first node
-    int gx, gy0;                            // the first node
-    // node sets as bits per row: live (in the grid, the window and not fixed),
-    // fill (the same with one row more above the window), own, nodes that a
-    // neighbour's window (edge) or set-up window (edge1: one ring more) holds
-    unsigned live = 0, fill = 0, own = 0, edge = 0, edge1 = 0;
-    // cells around the window that no thread's rows cover: node (-1: none), cell
-    constexpr int kRim = 2;
-    int rim_id[kRim], rim_cell[kRim];
-    ResCoef<NR> A;
-    double dinv[NR], cc[NR], r[NR], s[NR], w[NR];
+    ResGeo q;
+    ResLaneCtx x;
+    Control *ctl;
+    long long tmo;
+    double rtol;
+    int max_iter, coarse_iters, max_restarts;
+    bool verify;
+    int rows;
     {
         const Consts C = fetch(&Dp->C);
         const Bufs B = fetch(&Dp->B);
+        const LaunchInfo I = fetch(&Dp->I);
+        ctl = B.ctl;
+        tmo = C.timeout_ticks;
+        rtol = C.rtol;
+        max_iter = C.max_iter;
+        coarse_iters = fine ? 0 : C.coarse_iters;
+        verify = C.verify || C.fp32;
+        max_restarts = C.fp32 ? C.max_restarts : 2;
+        x.D = Dp;
+        x.gv0 = group_vec(B, G.vec, V_R0);
+        x.gvs = B.pool_stride;
+        x.trec = trec;
+        x.kind = L.kind;
+        x.slice = L.slice;
+        x.trace_steps = S.trace_stride - TR_HDR;
+        x.trunc = coarse_iters > 0;
+        x.leader = leader;
+        x.step = 0;
+        x.nsteps = lane_steps(C, L.kind);
+        x.sp_n = x.sp_j = x.sp_jprev = x.st_n = x.st_j = x.st_jprev = 0;
+        x.order = 0;
+        x.ext_cap = 1;
+        x.theta = x.src_scale = 0.0;
+        if (is_adj) {
+            const double Th = *B.Theta;
+            x.src_scale = C.plt ? (double)C.p / (double)C.Ne
+                                : pow_call(Th, 1.0 - C.p) / (double)C.Ne;
+            if (!(Th > 0.0) || !isfinite(Th)) set_status(ctl, -5);
+        }
+        if (L.kind == F_PRI) {
+            if (L.slice > 0 && !I.cold && !C.plt) x.theta = ipow(B.in_th[L.slice], C.p);
+        } else if (L.kind == GK_PRI) {
+            x.theta = B.in_th[L.slice];
+        }
+        // geometry: owned rectangle, window, this thread's column and rows
+        const int W = C.W, HN = C.ny + 1;
+        const int deg = coarse_iters > 0 ? 0 : L.deg;
+        const int TX = (W + L.tw - 1) / L.tw, TY = (HN + L.th - 1) / L.th;
+        const int hx = TX > 1 ? deg + 1 : 0, hy = TY > 1 ? deg + 1 : 0;
+        const int wc = L.tw + 2 * hx, wr = L.th + 2 * hy;
+        const int nq = min(kThreads / wc, (wr + NR - 1) / NR);
+        rows = nq * NR;
+        const int tq = tid / wc;
         const int tx = rank % TX, ty = rank / TX;  // ty >= TY: nothing owned
         const int ox0 = tx * L.tw, oy0 = ty * L.th;
         const int ox1 = min(ox0 + L.tw, W), oy1 = min(oy0 + L.th, HN);
-        gx = ox0 - hx + col;
-        gy0 = oy0 - hy + row0;
-        const bool inx = act && gx >= 0 && gx < W && ty < TY;
+        q.act = tq < nq;
+        const int col = q.act ? tid - tq * wc : 0, row0 = q.act ? tq * NR : 0;
+        q.W = W;
+        q.sz = wc + 2;
+        q.zlen = q.sz * (rows + 2);
+        q.cell0 = row0 * q.sz + col + 1;
+        q.gx = ox0 - hx + col;
+        q.gy0 = oy0 - hy + row0;
+        q.live = q.fill = q.own = q.edge = q.edge1 = 0;
+        const bool inx = q.act && q.gx >= 0 && q.gx < W && ty < TY;
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            const int y = gy0 + k, row = row0 + k;
+            const int y = q.gy0 + k, row = row0 + k;
             if (!inx || y < 0 || y >= HN || row > wr) continue;
-            const bool free_ = B.mask[(size_t)y * W + gx] == 0;
-            if (free_) fill |= 1u << k;
+            const bool free_ = B.mask[(size_t)y * W + q.gx] == 0;
+            if (free_) q.fill |= 1u << k;
             if (row >= wr) continue;
-            if (free_) live |= 1u << k;
-            if (gx >= ox0 && gx < ox1 && y >= oy0 && y < oy1) {
-                own |= 1u << k;
+            if (free_) q.live |= 1u << k;
+            if (q.gx >= ox0 && q.gx < ox1 && y >= oy0 && y < oy1) {
+                q.own |= 1u << k;
                 auto near = [&](int h) {
-                    return (tx > 0 && gx - ox0 < h) || (tx < TX - 1 && ox1 - gx <= h) ||
+                    return (tx > 0 && q.gx - ox0 < h) || (tx < TX - 1 && ox1 - q.gx <= h) ||
                            (ty > 0 && y - oy0 < h) || (ty < TY - 1 && oy1 - y <= h);
                 };
-                if (near(deg + 1)) edge |= 1u << k;
-                if (near(deg + 2)) edge1 |= 1u << k;
+                if (near(deg + 1)) q.edge |= 1u << k;
+                if (near(deg + 2)) q.edge1 |= 1u << k;
             }
         }
 #pragma unroll
         for (int i = 0; i < kRim; ++i) {
             const int e = tid + i * kThreads;
             int cx, cy;
-            if (e < 2 * sz) {
-                cx = e < sz ? e : e - sz;
-                cy = e < sz ? 0 : rows + 1;
+            if (e < 2 * q.sz) {
+                cx = e < q.sz ? e : e - q.sz;
+                cy = e < q.sz ? 0 : rows + 1;
             } else {
-                cx = (e & 1) ? sz - 1 : 0;
-                cy = 1 + ((e - 2 * sz) >> 1);
+                cx = (e & 1) ? q.sz - 1 : 0;
+                cy = 1 + ((e - 2 * q.sz) >> 1);
             }
-            const int x = ox0 - hx - 1 + cx, y = oy0 - hy - 1 + cy;
-            const bool in = e < 2 * sz + 2 * rows && x >= 0 && x < W && y >= 0 && y < HN &&
+            const int gx = ox0 - hx - 1 + cx, gy = oy0 - hy - 1 + cy;
+            const bool in = e < 2 * q.sz + 2 * rows && gx >= 0 && gx < W && gy >= 0 && gy < HN &&
                             cy <= wr + 1 && ty < TY;
-            const int id = in ? y * W + x : -1;
-            rim_id[i] = in && B.mask[id] == 0 ? id : -1;
-            rim_cell[i] = cy * sz + cx;
+            const int id = in ? gy * W + gx : -1;
+            q.rim_id[i] = in && B.mask[id] == 0 ? id : -1;
+            q.rim_cell[i] = cy * q.sz + cx;
         }
-        // coefficients: gap k lies below row k, its elements left and right of the
-        // column are (gx - 1, gy0 + k - 1) and (gx, gy0 + k - 1)
         const double ms = fine ? C.inv_dt : C.inv_dtau;
-        double sl = 0.0, sr = 0.0, xl = 0.0, xr = 0.0;
-#pragma unroll
-        for (int k = 0; k <= NR; ++k) {
-            const int ey = gy0 + k;  // padded element row
-            const bool in = inx && ey >= 0 && ey <= C.ny + 1;
-            const unsigned e = in ? (unsigned)(ey * C.EW + gx) : 0u;
-            const double ml = in ? *nd(B.cm, e) * ms : 0.0, mr = in ? *nd(B.cm, e + 1) * ms : 0.0;
-            const double kl = in ? *nd(B.kq, e) : 0.0, kr = in ? *nd(B.kq, e + 1) : 0.0;
-            A.dl[k] = ml + C.e_d * kl;
-            A.dr[k] = mr + C.e_d * kr;
-            A.nn[k] = 2.0 * (ml + mr) + C.e_y * (kl + kr);
-            const double nsl = 4.0 * ml + C.e_self * kl, nsr = 4.0 * mr + C.e_self * kr;
-            const double nxl = 2.0 * ml + C.e_x * kl, nxr = 2.0 * mr + C.e_x * kr;
-            if (k > 0) {
-                A.el[k - 1] = xl + nxl;
-                A.er[k - 1] = xr + nxr;
-                cc[k - 1] = (sl + sr) + (nsl + nsr);
-            }
-            sl = nsl;
-            sr = nsr;
-            xl = nxl;
-            xr = nxr;
-        }
-        const double *dinv_g = fine ? B.dinv_f : B.dinv_c;
-#pragma unroll
-        for (int k = 0; k < NR; ++k) {
-            const unsigned id = (live >> k) & 1u ? (unsigned)((gy0 + k) * W + gx) : 0u;
-            const double v = *nd(dinv_g, id);
-            dinv[k] = (live >> k) & 1u ? v : 0.0;
-            r[k] = s[k] = w[k] = 0.0;
-        }
         double lo, hi;
         res_bounds(C, __longlong_as_double((long long)ctl->kmin_bits) / ms,
                    __longlong_as_double((long long)ctl->kmax_bits) / ms, lo, hi);
         lds_sync();
         if (tid <= deg) om_s[tid] = res_omega(lo, hi, deg, tid);
-        // both operand windows: every cell outside the grid stays 0
-        for (int c = tid; c < 2 * zlen; c += kThreads) lds[c] = 0.0;
-#pragma unroll
-        for (int k = 0; k < 2 * NR; ++k) LP[k * kThreads] = 0.0;
+        // operand windows: every cell outside the grid stays 0; p and x slots
+        for (int c = tid; c < 2 * q.zlen + 2 * NR * kThreads; c += kThreads) lds[c] = 0.0;
         lds_sync();
     }
-    const int n0 = gy0 * W + gx;
+    const bool trunc = coarse_iters > 0;
+    const int deg = trunc ? 0 : L.deg;
+    const int cell0 = q.cell0, sz = q.sz, zlen = q.zlen, W = q.W;
+    const int LP = q.slot_p<NR>(), LX = q.slot_x<NR>();
+    const unsigned live = q.live, own = q.own, edge = q.edge, edge1 = q.edge1;
+    const bool act = q.act;
+    const int n0 = q.gy0 * W + q.gx;
+    const double *gv0 = x.gv0;
+    const size_t gvs = x.gvs;
+    const int nsteps = x.nsteps;
     auto id_of = [&](int k) { return (unsigned)(fresh(n0) + k * W); };
-    auto is = [](unsigned m, int k) { return (((unsigned)fresh((int)m) >> k) & 1u) != 0; };
+    auto is = [](unsigned m, int k) { return ResGeo::is(m, k); };
+    ResCoef<NR> A;
+    double dinv[NR], cc[NR], r[NR], s[NR], w[NR];
 
     ResTimers tm;
     if constexpr (TIMED) tm.mark = now_ticks();
@@ -371,35 +963,21 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         }
         return ok;
     };
-    auto waitf = [&](int idx) -> bool {
-        long long t0 = 0;
-        if constexpr (TIMED) t0 = now_ticks();
-        const Bufs B = fetch(&Dp->B);
-        const LaunchInfo I = fetch(&Dp->I);
-        const bool ok = wait_flag(B.flags, idx, I.epoch, ctl, tmo);
-        if constexpr (TIMED) {
-            const long long t1 = now_ticks();
-            tm.work += t0 - tm.mark;
-            tm.flag += t1 - t0;
-            tm.mark = t1;
-        }
-        return ok;
-    };
     // this workgroup's Q sums to its partial slots of the coming barrier
     auto put_sums = [&](auto &v) {
         constexpr int Q = sizeof(v) / sizeof(double);
         const int t = fresh(tid), wave = t >> 6;
 #pragma unroll
         for (int k = 0; k < Q; ++k) {
-            const double x = wave_sum(v[k]);
-            if ((t & 63) == 0) red[k * kWaves + wave] = x;
+            const double y = wave_sum(v[k]);
+            if ((t & 63) == 0) red[k * kWaves + wave] = y;
         }
         lds_sync();
         if (t < Q) {
-            double x = 0.0;
+            double y = 0.0;
 #pragma unroll
-            for (int k = 0; k < kWaves; ++k) x += red[t * kWaves + k];
-            stc(part + ((size_t)(nbar & 1) * kResSums + t) * kResGroup + rank, x);
+            for (int k = 0; k < kWaves; ++k) y += red[t * kWaves + k];
+            stc(part + ((size_t)(nbar & 1) * kResSums + t) * kResGroup + rank, y);
         }
     };
     // the group's sums after the barrier: wave k adds component k
@@ -408,10 +986,10 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         const int t = fresh(tid), wave = t >> 6, ln = t & 63;
         if (wave < Q) {
             const double *p = part + ((size_t)((nbar - 1) & 1) * kResSums + wave) * kResGroup;
-            double x = 0.0;
-            for (int k = ln; k < g; k += 64) x += ldc(p + k);
-            x = wave_sum(x);
-            if (ln == 0) tot_s[wave] = x;
+            double y = 0.0;
+            for (int k = ln; k < g; k += 64) y += ldc(p + k);
+            y = wave_sum(y);
+            if (ln == 0) tot_s[wave] = y;
         }
         lds_sync();
 #pragma unroll
@@ -421,40 +999,6 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
             tm.red += t1 - tm.mark;
             tm.mark = t1;
         }
-    };
-    // A row of global values at the thread's nodes in m, all loads in flight at
-    // once: no load is conditional (the other nodes read node 0), since a masked
-    // load whose value is used in its own branch waits for it there, node by node.
-    auto load = [&](const double *row, unsigned m, double (&v)[NR]) {
-#pragma unroll
-        for (int k = 0; k < NR; ++k) v[k] = ldg(row, is(m, k) ? id_of(k) : 0u);
-    };
-    auto load_rim = [&](const double *row, double (&v)[kRim]) {
-#pragma unroll
-        for (int i = 0; i < kRim; ++i) v[i] = ldg(row, rim_id[i] >= 0 ? (unsigned)rim_id[i] : 0u);
-    };
-    // the operand window at LDS index zb
-    auto put_win = [&](int zb, const double (&v)[NR], const double (&vr)[kRim]) {
-        if (act) {
-#pragma unroll
-            for (int k = 0; k < NR; ++k) lds[zb + cell0 + (k + 1) * sz] = is(fill, k) ? v[k] : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < kRim; ++i)
-            if (rim_id[i] >= 0) lds[zb + rim_cell[i]] = vr[i];
-    };
-    auto store = [&](const double *row, unsigned m, const double (&v)[NR]) {
-#pragma unroll
-        for (int k = 0; k < NR; ++k)
-            if (is(m, k)) *nd(row, id_of(k)) = v[k];
-    };
-    // x of the finished solve on the window (and its rim): own values from the
-    // thread's slots, the others as their owners published them
-    auto load_x = [&](const double *xp, double (&v)[NR], double (&vr)[kRim]) {
-        load(xp, fill & ~own, v);
-        load_rim(xp, vr);
-#pragma unroll
-        for (int k = 0; k < NR; ++k) v[k] = is(own, k) ? LX[k * kThreads] : v[k];
     };
     // u = q(D^{-1}A) D^{-1} r; leaves u in operand window zc_buf, w = A u in w
     // and adds (r, u) and (u, w) of the owned nodes
@@ -487,48 +1031,39 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         zc_buf = b;
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            w[k] = dinv[k] != 0.0 ? cc[k] * zc[k] - t[k] : 0.0;
             const double u = is(own, k) ? zc[k] : 0.0;
+            w[k] = is(live, k) ? cc[k] * zc[k] - t[k] : 0.0;
             gam += r[k] * u;
             del += u * w[k];
         }
     };
-    // w of the window's other nodes, published in the round of the last barrier
-    auto halo_w = [&]() {
-        const double *P = wv(nbar - 1);
-        double h[NR];
-        load(P, live & ~own, h);
-#pragma unroll
-        for (int k = 0; k < NR; ++k) w[k] = is(live & ~own, k) ? h[k] : w[k];
-    };
-    auto publish_x = [&](int j) {
-        const double *row = xh(j);
+    auto publish_w = [&]() {
+        const double *P = res_w(gv0, gvs, nbar);
 #pragma unroll
         for (int k = 0; k < NR; ++k)
-            if (is(edge1, k)) stg(row, id_of(k), LX[k * kThreads]);
+            if (is(edge, k)) stg(P, id_of(k), w[k]);
+    };
+    // w of the window's other nodes, published in the round of the last barrier
+    auto halo_w = [&]() {
+        const double *P = res_w(gv0, gvs, nbar - 1);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const bool in = is(live & ~own, k);
+            const double v = ldg(P, in ? id_of(k) : 0u);
+            w[k] = in ? v : w[k];
+        }
+    };
+    auto publish_x = [&](int j) {
+        const double *row = res_x(gv0, gvs, j);
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            if (is(edge1, k)) stg(row, id_of(k), lds[LX + k * kThreads]);
     };
 
-    double theta = 0.0, src_scale = 0.0;
-    int nsteps;
-    {
-        const Consts C = fetch(&Dp->C);
-        const Bufs B = fetch(&Dp->B);
-        const LaunchInfo I = fetch(&Dp->I);
-        nsteps = lane_steps(C, L.kind);
-        if (is_adj) {
-            const double Th = *B.Theta;
-            src_scale = C.plt ? (double)C.p / (double)C.Ne
-                              : pow_call(Th, 1.0 - C.p) / (double)C.Ne;
-            if (!(Th > 0.0) || !isfinite(Th)) set_status(ctl, -5);
-        }
-        if (L.kind == F_PRI) {
-            if (L.slice > 0 && !I.cold && !C.plt) theta = B.in_th[L.slice];
-        } else if (L.kind == GK_PRI) {
-            theta = B.in_th[L.slice];
-        }
-    }
     const unsigned nbar0 = nbar;
     unsigned long long iters_all = 0;
+    int iters_max = 0;
+    long long relres_max = 0;  // as double bits, so that a NaN counts as the largest
     if (leader) {
         trec[TR_KIND] = L.kind;
         trec[TR_SLICE] = L.slice;
@@ -537,480 +1072,98 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         trec[TR_START] = (unsigned long long)now_ticks();
     }
 
-    // the solve last set up (number `step`, 1..nsteps) and its progress
-    enum { SETUP, RESTART, ITER };
-    int mode = SETUP, step = 0;
-    int sp_n = 0, sp_j = 0, sp_jprev = 0, st_n = 0, st_j = 0, st_jprev = 0;
+    {
+        const Consts C = fetch(&Dp->C);
+        const Bufs B = fetch(&Dp->B);
+        q.coefs<NR>(C, B, fine, A, cc);
+        const double *dg = fine ? B.dinv_f : B.dinv_c;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const double d = *nd(dg, is(live, k) ? id_of(k) : 0u);
+            dinv[k] = is(live, k) ? d : 0.0;
+        }
+    }
+    int step = 0;
     double bnorm = 0.0, relres = 0.0, rnorm = 0.0, alpha = 0.0, beta = 0.0, gamma = 0.0;
-    int iter = 0, restarts = 0, ext_cap = 1, order = 0;
-    bool capped = false, first = true, shown = false;
+    int iter = 0, restarts = 0;
+    bool capped = false, restart = false;
     for (;;) {
-        const bool prev = step > 0, next = step < nsteps, last = prev && !next;
-        // x of solve `step` is kept in history slot `step` once it is finished
-        const double *xp = xh(step);
-        // sums: SETUP residual, ||x||_p^p, b, r0, (r, u), (u, w), plain start's r0;
-        // otherwise (r, u), (u, w), (r, r)
-        double sum[7] = {0, 0, 0, 0, 0, 0, 0};
-        if (mode == ITER) {
-            // s = w + beta s, p = u + beta p, x += alpha p, r -= alpha s (p and x
-            // of nodes that are not owned are formed too, and never read)
+        // ---- set-up or restart, then the first u, w and sums ------------------------
+        const bool prev = step > 0, last = prev && step == nsteps;
+        double sum[3] = {0.0, 0.0, 0.0};  // (r, u), (u, w), (r, r)
+        x.step = step;
+        if (!restart) {
+            if (!res_setup<NR>(q, x, A, cc)) return false;
+        } else {
+            res_residual<NR>(q, x, A, cc);
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
-                const double u = lds[zc_buf * zlen + cell0 + (k + 1) * sz];
-                const double p0 = LP[k * kThreads], x0 = LX[k * kThreads];
-                s[k] = first ? w[k] : w[k] + beta * s[k];
-                const double pn = first ? u : u + beta * p0;
-                LP[k * kThreads] = pn;
-                LX[k * kThreads] = x0 + alpha * pn;
-                r[k] -= alpha * s[k];
-                const double ro = is(own, k) ? r[k] : 0.0;
-                sum[2] += ro * ro;
-            }
-        } else if (mode == RESTART) {
-            // CG anew from the true residual of x: the owned values cross to the
-            // neighbours' windows first
-            double zc[NR], t[NR], v[NR], vr[kRim];
-            load(xp, fill | own, v);
-            load_rim(xp, vr);
-#pragma unroll
-            for (int k = 0; k < NR; ++k) LX[k * kThreads] = v[k];
-            put_win(0, v, vr);
-            load(bvec(step), own & live, v);
-            lds_sync();
-            res_apply<NR>(A, cell0, sz, v, zc, t);
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                w[k] = is(live & own, k) ? t[k] - cc[k] * zc[k] : 0.0;
+                const double v = lds[zlen + cell0 + (k + 1) * sz];
+                w[k] = act ? v : 0.0;
                 sum[2] += w[k] * w[k];
-                if (is(edge, k)) stg(wv(nbar), id_of(k), w[k]);
             }
+            // the residual's owned values cross to the neighbours' windows
+            publish_w();
             if (!barrier(false)) return false;
             halo_w();
+            if (act) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) r[k] = w[k];
-            zc_buf = 0;
-        } else {
-            const Consts C = fetch(&Dp->C);
-            const Bufs B = fetch(&Dp->B);
-            const LaunchInfo I = fetch(&Dp->I);
-            const size_t Nn = C.Nn;
-            StepInfo st{};
-            if (next) {
-                st = step_info(C, B, I, L, step, xp);
-                st_n = st.n;
-                st_j = st.j;
-                st_jprev = st.jprev;
-            }
-            // waits: the guess of a cold-started slice; what a sweep's step reads
-            if (next && st.wait) {
-                if (!waitf(st.wait_idx)) return false;
-                if (L.kind == F_PRI && I.cold && L.slice > 0) theta = ldc(B.Gk_th + L.slice - 1);
-            }
-            if (sweep) {
-                if (step == 0) {
-                    if (!waitf(flag_index(FL_F, L.kind == SWEEP_PRI ? 0 : C.Ntau))) return false;
-                    if (L.kind == SWEEP_PRI) theta = ldc(B.F_th);
-                } else if (!waitf(flag_index(FL_F, sp_n))) {
-                    return false;
-                }
-                if (next && (I.cold || I.gk_lanes))
-                    if (!waitf(flag_index(I.cold ? FL_COLD : FL_GK, st.n))) return false;
-            }
-            // window 0: x of the finished solve, window 1: the operand tp of the
-            // next right-hand side where it is another vector (a sweep's next input
-            // u = x + F_n - G(u^k_n), a lane's first input)
-            double zc[NR], t[NR], v[NR], bv[NR], vr[kRim], br[kRim];
-            zc_buf = 0;
-            if (prev) {
-                load_x(xp, v, vr);
-                load(bvec(step), own & live, bv);
-                if (sweep) {
-                    const double *Fp = L.kind == SWEEP_PRI
-                                           ? B.S + (size_t)(C.M * (sp_n + 1) - 1) * Nn
-                                           : B.FL + (size_t)sp_n * Nn;
-                    const double *Gp = B.Gk + (size_t)sp_n * Nn;
-                    double fr[kRim], gr[kRim];
-                    load(Fp, fill, zc);
-                    load(Gp, fill, t);
-                    load_rim(Fp, fr);
-                    load_rim(Gp, gr);
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) zc[k] = v[k] + (zc[k] - t[k]);
-#pragma unroll
-                    for (int i = 0; i < kRim; ++i) br[i] = vr[i] + (fr[i] - gr[i]);
-                    put_win(zlen, zc, br);
-                }
-                put_win(0, v, vr);
-            } else {
-                load(st.tp_src, fill, v);
-                load_rim(st.tp_src, vr);
-                put_win(zlen, v, vr);
-#pragma unroll
-                for (int i = 0; i < kRim; ++i) br[i] = vr[i];
-            }
-            lds_sync();
-            if (prev) {
-                // ---- the finished solve: true residual and outputs --------------
-                res_apply<NR>(A, cell0, sz, bv, zc, t);
-#pragma unroll
-                for (int k = 0; k < NR; ++k) {
-                    const double rv = is(live & own, k) ? t[k] - cc[k] * zc[k] : 0.0;
-                    sum[0] += rv * rv;
-                }
-                // zc: x at the thread's nodes
-#pragma unroll
-                for (int k = 0; k < NR; ++k)
-                    if (is(own, k)) stg(xp, id_of(k), zc[k]);
-                if (!is_adj) {
-#pragma unroll
-                    for (int k = 0; k < NR; ++k)
-                        sum[1] += ipow(is(own, k) ? zc[k] : 0.0, C.p);
-                }
-                if (L.kind == F_PRI) {
-                    store(B.S + (size_t)(sp_j - 1) * Nn, own, zc);
-                    if (C.plt && last) store(B.out_T + (size_t)(L.slice + 1) * Nn, own, zc);
-                } else if (L.kind == F_ADJ) {
-                    if (last) store(B.FL + (size_t)L.slice * Nn, own, zc);
-                    if (C.plt && last) store(B.out_L + (size_t)(L.slice - 1) * Nn, own, zc);
-                } else {
-                    store((sweep ? B.Gn : B.Gk) + (size_t)sp_n * Nn, own, zc);
-                }
-                if (sweep) {
-                    // (the slice-end slot of S, still read as F_n by the neighbours
-                    // in this round, follows after the barrier)
-                    const double *row = L.kind == SWEEP_PRI ? B.out_T + (size_t)(sp_n + 1) * Nn
-                                                            : B.out_L + (size_t)(sp_n - 1) * Nn;
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) v[k] = lds[zlen + cell0 + (k + 1) * sz];
-                    store(row, own, v);
-                }
-                if (L.kind == F_ADJ || L.kind == SWEEP_ADJ) {
-                    // sensitivity terms of the elements right above the owned nodes;
-                    // they wait in p's slots until the residual has been accepted
-                    const double *Tr = B.S + (size_t)(sp_j - 1) * Nn;
-                    const double *Tp = sp_jprev > 0 ? B.S + (size_t)(sp_jprev - 1) * Nn : nullptr;
-                    const double *Gp = B.Gk + (size_t)sp_n * Nn;
-                    const int gxf = fresh(gx), gyf = fresh(gy0);
-                    const double idl = fine ? C.inv_dt : C.inv_dtau;
-                    auto corner = [&](const double *row, int k, int dx) {
-                        const int y = gyf + k;
-                        const bool in = act && gxf >= 0 && gxf + dx < W && y >= 0 && y < HN;
-                        return *nd(row, in ? (unsigned)(y * W + gxf + dx) : 0u);
-                    };
-                    // lower corners of the element row, left and right
-                    double ta = corner(Tr, 0, 0), tb = corner(Tr, 0, 1), pa = 0.0, pb = 0.0;
-                    if (I.has_dc && Tp) {
-                        pa = corner(Tp, 0, 0);
-                        pb = corner(Tp, 0, 1);
-                    }
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) {
-                        const double tc = corner(Tr, k + 1, 0), td = corner(Tr, k + 1, 1);
-                        const int y = gyf + k;
-                        const bool el = is(own, k) && gxf < C.nx && y < C.ny;
-                        const unsigned e = el ? (unsigned)(y * C.nx + gxf) : 0u;
-                        const int z = cell0 + (k + 1) * sz;
-                        double l0 = lds[z], l1 = lds[z + 1], l2 = lds[z + sz + 1], l3 = lds[z + sz];
-                        if (sweep) {
-                            const unsigned id = el ? id_of(k) : 0u;
-                            const unsigned up = el ? id + W : 0u;
-                            l0 -= ldg(Gp, id);
-                            l1 -= ldg(Gp, id + 1);
-                            l2 -= ldg(Gp, up + 1);
-                            l3 -= ldg(Gp, up);
-                        }
-                        double term = *nd(B.dk, e) * elem_k(C, l0, l1, l2, l3, ta, tb, td, tc);
-                        if (I.has_dc) {
-                            double pc = 0.0, pd = 0.0;
-                            if (Tp) {
-                                pc = corner(Tp, k + 1, 0);
-                                pd = corner(Tp, k + 1, 1);
-                            }
-                            term += *nd(B.dc, e) * idl *
-                                    elem_c(C, l0, l1, l2, l3, ta - pa, tb - pb, td - pd, tc - pc);
-                            pa = pc;
-                            pb = pd;
-                        }
-                        LP[k * kThreads] = term;
-                        ta = tc;
-                        tb = td;
-                    }
-                }
-            }
-            if (next) {
-                // ---- the next solve: b, x0, r0 ----------------------------------
-                // states of the slice before this one extrapolate; differences that
-                // reach back to the slice's given first state, which may be off in
-                // its rough modes, are not used
-                order = 0;
-                if (fine && C.extrap) order = step >= 2 ? 1 : 0;
-                else if (fine && prev) order = max(0, min(min(step - 2, 3), ext_cap));
-                const int gxf = fresh(gx), gyf = fresh(gy0);
-                const bool inx = act && gxf >= 0 && gxf < W;
-                // source
-                if (st.adjoint) {
-                    load(B.S + (size_t)(st.j - 1) * Nn, live, bv);
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) bv[k] = src_scale * ipow(bv[k], C.p - 1);
-                } else {
-                    const double f = B.qt[st.j] * C.quarter_area * (double)((gxf > 0) + (gxf < C.nx));
-#pragma unroll
-                    for (int k = 0; k < NR; ++k)
-                        bv[k] = f * (double)((gyf + k > 0) + (gyf + k < C.ny));
-                }
-                {
-                    // + (C/delta) tp on the window
-                    const double ms = fine ? C.inv_dt : C.inv_dtau;
-                    int z = (prev && !sweep ? 0 : zlen) + cell0;
-                    auto elem = [&](int k, int dx) {
-                        const int ey = gyf + k;
-                        const bool in = inx && ey >= 0 && ey <= C.ny + 1;
-                        const double m = *nd(B.cm, in ? (unsigned)(ey * C.EW + gxf + dx) : 0u);
-                        return in ? m * ms : 0.0;
-                    };
-                    double ml0 = elem(0, 0), mr0 = elem(0, 1);
-                    double l0 = lds[z - 1], c0 = lds[z], r0 = lds[z + 1];
-                    z += sz;
-                    double l1 = lds[z - 1], c1 = lds[z], r1 = lds[z + 1];
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) {
-                        z += sz;
-                        const double l2 = lds[z - 1], c2 = lds[z], r2 = lds[z + 1];
-                        const double ml1 = elem(k + 1, 0), mr1 = elem(k + 1, 1);
-                        double m = 4.0 * ((ml0 + mr0) + (ml1 + mr1)) * c1;
-                        m += 2.0 * ((mr0 + mr1) * r1 + (ml0 + ml1) * l1 + (ml1 + mr1) * c2 +
-                                    (ml0 + mr0) * c0);
-                        m += mr1 * r2 + ml1 * l2 + mr0 * r0 + ml0 * l0;
-                        bv[k] = is(live, k) ? m + bv[k] : 0.0;
-                        l0 = l1;
-                        c0 = c1;
-                        r0 = r1;
-                        l1 = l2;
-                        c1 = c2;
-                        r1 = r2;
-                        ml0 = ml1;
-                        mr0 = mr1;
-                    }
-                }
-                if (order > 0) {
-                    // residual of the plain start x0 = x: it judges the extrapolation
-                    res_apply<NR>(A, cell0, sz, bv, zc, t);
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) {
-                        const double rv = is(live & own, k) ? t[k] - cc[k] * zc[k] : 0.0;
-                        sum[6] += rv * rv;
-                    }
-                    // x0 from x and the states before it
-                    double a[NR], ar[kRim];
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) v[k] = lds[cell0 + (k + 1) * sz];
-                    load(xh(step - 1), fill, a);
-                    load_rim(xh(step - 1), ar);
-                    const double ca = order == 1 ? 2.0 : order == 2 ? 3.0 : 4.0;
-                    const double cb = order == 1 ? -1.0 : order == 2 ? -3.0 : -6.0;
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) v[k] = ca * v[k] + cb * a[k];
-#pragma unroll
-                    for (int i = 0; i < kRim; ++i) vr[i] = ca * vr[i] + cb * ar[i];
-                    if (order > 1) {
-                        load(xh(step - 2), fill, a);
-                        load_rim(xh(step - 2), ar);
-                        const double cd = order == 2 ? 1.0 : 4.0;
-#pragma unroll
-                        for (int k = 0; k < NR; ++k) v[k] += cd * a[k];
-#pragma unroll
-                        for (int i = 0; i < kRim; ++i) vr[i] += cd * ar[i];
-                    }
-                    if (order > 2) {
-                        load(xh(step - 3), fill, a);
-                        load_rim(xh(step - 3), ar);
-#pragma unroll
-                        for (int k = 0; k < NR; ++k) v[k] -= a[k];
-#pragma unroll
-                        for (int i = 0; i < kRim; ++i) vr[i] -= ar[i];
-                    }
-                } else if (!prev || sweep) {
-                    // x0 from the step's description; uc, br: its operand tp
-                    double uc[NR];
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) uc[k] = lds[zlen + cell0 + (k + 1) * sz];
-                    if (trunc) {
-#pragma unroll
-                        for (int k = 0; k < NR; ++k) v[k] = uc[k];
-#pragma unroll
-                        for (int i = 0; i < kRim; ++i) vr[i] = br[i];
-                    } else {
-                        load(st.x0_src, fill, v);
-                        load_rim(st.x0_src, vr);
-                        if (st.d1) {
-                            double a[NR], ar[kRim];
-                            load(st.d0, fill, a);
-                            load_rim(st.d0, ar);
-#pragma unroll
-                            for (int k = 0; k < NR; ++k) v[k] += uc[k] - a[k];
-#pragma unroll
-                            for (int i = 0; i < kRim; ++i) vr[i] += br[i] - ar[i];
-                        }
-                    }
-                    if (!prev && sweep) {
-                        // what the sweep publishes of its input
-                        store(L.kind == SWEEP_PRI ? B.out_T + Nn
-                                                  : B.out_L + (size_t)(C.Ntau - 1) * Nn,
-                              own, uc);
-                        if (is_adj) {
-#pragma unroll
-                            for (int k = 0; k < NR; ++k) uc[k] = 0.0;
-                            store(B.out_L + (size_t)C.Ntau * Nn, own, uc);
-                        }
-                    }
-                }
-                if (!prev || sweep || order > 0) {
-                    lds_sync();
-                    put_win(0, v, vr);
-                    lds_sync();
-                }
-                res_apply<NR>(A, cell0, sz, bv, zc, t);
-#pragma unroll
-                for (int k = 0; k < NR; ++k) {
-                    r[k] = is(live, k) ? t[k] - cc[k] * zc[k] : 0.0;
-                    // x of the new solve (the finished x is in the history)
-                    LX[k * kThreads] = zc[k];
-                    const double bo = is(own, k) ? bv[k] : 0.0, ro = is(own, k) ? r[k] : 0.0;
-                    sum[2] += bo * bo;
-                    sum[3] += ro * ro;
-                }
-                store(bvec(step + 1), own, bv);
-                lds_sync();  // both operand windows have been read
+                for (int k = 0; k < NR; ++k) lds[zlen + cell0 + (k + 1) * sz] = w[k];
             }
         }
-        // ---- every round: u, w, the sums, w's and x's edges, the barrier -----------
-        const bool setup = mode == SETUP;
-        if (!last || !setup) {
-            precond(sum[setup ? 4 : 0], sum[setup ? 5 : 1]);
-            const double *P = wv(nbar);
 #pragma unroll
-            for (int k = 0; k < NR; ++k)
-                if (is(edge, k)) stg(P, id_of(k), w[k]);
+        for (int k = 0; k < NR; ++k) {
+            const double v = lds[zlen + cell0 + (k + 1) * sz];
+            r[k] = is(live, k) ? v : 0.0;
+            s[k] = w[k] = 0.0;
         }
-        double tot[7];
-        if (setup) {
-            put_sums(sum);
+        zc_buf = 0;
+        if (!last || restart) {
+            precond(sum[0], sum[1]);
+            publish_w();
+        }
+        bool closed = false;  // x of the current solve is final
+        if (!restart) {
+            double tot[7];
+#pragma unroll
+            for (int k = 0; k < 7; ++k) tot[k] = x.sum[k];
+            tot[4] = sum[0];
+            tot[5] = sum[1];
+            put_sums(tot);
             // release: rows that other lanes read once this round's flags are set
             if (!barrier(prev && (last || L.kind == COLD_PRI || L.kind == COLD_ADJ))) return false;
             if (!last) halo_w();
             get_sums(tot);
-        } else {
-            // near the end x's edge goes out too, so that the round that closes the
-            // solve can start at once (a round gains about a decimal digit)
-            const int nit = iter + 1;
-            shown = mode == ITER && (trunc ? nit >= coarse_iters
-                                           : rnorm <= 200.0 * rtol * bnorm || nit >= max_iter);
-            if (shown) publish_x(step);
-            double s3[3] = {sum[0], sum[1], sum[2]};
-            put_sums(s3);
-            if (!barrier(false)) return false;
-            halo_w();
-            get_sums(s3);
-            tot[0] = s3[0];
-            tot[1] = s3[1];
-            tot[2] = s3[2];
-        }
-        // ---- decisions ---------------------------------------------------------------
-        bool closed = false;  // x of the current solve is final
-        if (setup) {
-            const Consts C = fetch(&Dp->C);
-            const Bufs B = fetch(&Dp->B);
-            bool again = false;
-            if (prev && !trunc && !capped && bnorm > 0.0 && (C.verify || C.fp32)) {
+            if (prev && !trunc && !capped && bnorm > 0.0 && verify) {
                 // the true residual decides
                 const double rn = sqrt(tot[0]);
                 relres = rn / bnorm;
                 if (!(rn <= rtol * bnorm)) {
-                    if (restarts >= (C.fp32 ? C.max_restarts : 2) || iter >= max_iter) {
-                        if (leader) set_status(ctl, -4);
-                    } else {
-                        again = true;
+                    if (restarts < max_restarts && iter < max_iter) {
+                        ++restarts;
+                        restart = true;
+                        continue;
                     }
+                    if (leader) set_status(ctl, -4);
                 }
-            }
-            if (again) {
-                ++restarts;
-                mode = RESTART;
-                continue;
             }
             if (prev) {
-                // ---- the finished solve's sums and flags -------------------------
-                if (L.kind == F_ADJ || L.kind == SWEEP_ADJ) {
-                    const double *ac = fine ? B.acc + (size_t)(L.slice - 1) * C.Ne : B.accG;
-                    const int gxf = fresh(gx), gyf = fresh(gy0);
-                    double a[NR];
-                    auto el = [&](int k) { return is(own, k) && gxf < C.nx && gyf + k < C.ny; };
-                    auto eid = [&](int k) { return (unsigned)((gyf + k) * C.nx + gxf); };
-                    if (step > 1) {
-#pragma unroll
-                        for (int k = 0; k < NR; ++k) a[k] = *nd(ac, el(k) ? eid(k) : 0u);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < NR; ++k) a[k] = 0.0;
-                    }
-#pragma unroll
-                    for (int k = 0; k < NR; ++k)
-                        if (el(k)) *nd(ac, eid(k)) = a[k] + LP[k * kThreads];
-                }
-                if (L.kind == SWEEP_PRI) {
-                    double u[NR];
-                    const double *row = B.out_T + (size_t)(sp_n + 1) * C.Nn;
-#pragma unroll
-                    for (int k = 0; k < NR; ++k) u[k] = *nd(row, is(own, k) ? id_of(k) : 0u);
-                    store(B.S + (size_t)(C.M * (sp_n + 1) - 1) * C.Nn, own, u);
-                }
-                if (!is_adj) {
-                    const double inv = fine ? C.inv_NtNe : C.inv_NtauNe;
-                    // with G = 0 a fine lane keeps its slice's part of Theta~ instead
-                    const double thG = C.plt ? theta + tot[1] * inv
-                                             : pow_call(ipow(theta, C.p) + tot[1] * inv, C.inv_p);
-                    if (L.kind == SWEEP_PRI) {
-                        const double thu = thG + ldc(B.F_th + sp_n) - ldc(B.Gk_th + sp_n);
-                        if (leader) {
-                            B.out_th[sp_n + 1] = thu;
-                            B.Gn_th[sp_n] = thG;
-                        }
-                        theta = thu;
-                    } else {
-                        theta = thG;
-                        if (leader && !fine) B.Gk_th[sp_n] = thG;
-                        if (leader && fine && last) B.F_th[L.slice] = thG;
-                    }
-                }
-                if (leader) {
-                    const unsigned epoch = fetch(&Dp->I).epoch;
-                    atomicAdd(fine ? &ctl->iters_fine : &ctl->iters_coarse,
-                              (unsigned long long)iter);
-                    atomicAdd(fine ? &ctl->solves_fine : &ctl->solves_coarse, 1ull);
-                    atomicMax(&ctl->max_iters, iter);
-                    atomicMax(&ctl->max_relres_bits,
-                              (unsigned long long)__double_as_longlong(relres));
-                    if (L.kind == GK_PRI || L.kind == GK_ADJ)
-                        set_flag(B.flags, flag_index(FL_GK, sp_n), epoch);
-                    if (L.kind == COLD_PRI || L.kind == COLD_ADJ)
-                        set_flag(B.flags, flag_index(FL_COLD, sp_n), epoch);
-                    if (fine && last) set_flag(B.flags, flag_index(FL_F, L.slice), epoch);
-                    if (step - 1 < S.trace_stride - TR_HDR)
-                        trec[TR_HDR + step - 1] = (unsigned long long)now_ticks();
-                }
+                res_commit<NR>(q, x, tot[1]);
                 iters_all += iter;
+                iters_max = max(iters_max, iter);
+                relres_max = max(relres_max, __double_as_longlong(relres));
             } else if (leader && L.kind == SWEEP_PRI) {
-                B.out_th[1] = theta;
+                fetch(&Dp->B).out_th[1] = x.theta;
             }
             if (last) break;
             // ---- the next solve becomes the current one --------------------------
-            ext_cap = order == 0 ? 1 : tot[3] > tot[6] ? order - 1 : order + 1;
-            sp_n = st_n;
-            sp_j = st_j;
-            sp_jprev = st_jprev;
+            x.ext_cap = x.order == 0 ? 1 : tot[3] > tot[6] ? x.order - 1 : x.order + 1;
+            x.sp_n = x.st_n;
+            x.sp_j = x.st_j;
+            x.sp_jprev = x.st_jprev;
             ++step;
             iter = restarts = 0;
-            capped = shown = false;
+            capped = false;
             bnorm = sqrt(tot[2]);
             rnorm = sqrt(tot[3]);
             relres = bnorm > 0.0 ? rnorm / bnorm : 0.0;
@@ -1021,44 +1174,77 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
             } else if (bnorm == 0.0) {
                 closed = true;
 #pragma unroll
-                for (int k = 0; k < NR; ++k) LX[k * kThreads] = 0.0;
+                for (int k = 0; k < NR; ++k) lds[LX + k * kThreads] = 0.0;
             } else {
                 closed = rnorm <= rtol * bnorm;
             }
-            mode = ITER;
-            first = true;
-        } else if (mode == RESTART) {
-            gamma = tot[0];
-            alpha = tot[0] / tot[1];
-            rnorm = sqrt(tot[2]);
-            mode = ITER;
-            first = true;
         } else {
-            iter += 1;
-            rnorm = sqrt(tot[2]);
-            const double target = rtol * bnorm;
+            put_sums(sum);
+            if (!barrier(false)) return false;
+            halo_w();
+            get_sums(sum);
+            rnorm = sqrt(sum[2]);
+            gamma = sum[0];
+            alpha = sum[0] / sum[1];
+            restart = false;
+        }
+        // ---- the rounds of CG, a loop of its own: what only the set-up needs is kept
+        // out of its registers --------------------------------------------------------
+        beta = 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) lds[LP + k * kThreads] = 0.0;
+        bool shown = false;
+        while (!closed) {
+            // s = w + beta s, p = u + beta p, x += alpha p, r -= alpha s (p and x
+            // of nodes that are not owned are formed too, and never read)
+            sum[0] = sum[1] = sum[2] = 0.0;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                const double u = lds[zc_buf * zlen + cell0 + (k + 1) * sz];
+                const double p0 = lds[LP + k * kThreads], x0 = lds[LX + k * kThreads];
+                s[k] = w[k] + beta * s[k];
+                const double pn = u + beta * p0;
+                lds[LP + k * kThreads] = pn;
+                lds[LX + k * kThreads] = x0 + alpha * pn;
+                r[k] -= alpha * s[k];
+                const double ro = is(own, k) ? r[k] : 0.0;
+                sum[2] += ro * ro;
+            }
+            precond(sum[0], sum[1]);
+            publish_w();
+            // near the end x's edge goes out too, so that the round that closes the
+            // solve can start at once (a round gains about a decimal digit)
+            ++iter;
+            shown = trunc ? iter >= coarse_iters
+                          : rnorm <= 200.0 * rtol * bnorm || iter >= max_iter;
+            if (shown) publish_x(step);
+            put_sums(sum);
+            if (!barrier(false)) return false;
+            halo_w();
+            get_sums(sum);
+            rnorm = sqrt(sum[2]);
             if (trunc ? (iter >= coarse_iters || rnorm == 0.0)
-                      : (rnorm <= target || iter >= max_iter)) {
+                      : (rnorm <= rtol * bnorm || iter >= max_iter)) {
                 relres = bnorm > 0.0 ? rnorm / bnorm : 0.0;
-                capped = !trunc && !(rnorm <= target);
-                if (capped && rnorm > target && leader) set_status(ctl, -4);
+                capped = !trunc && !(rnorm <= rtol * bnorm);
+                if (capped && rnorm > rtol * bnorm && leader) set_status(ctl, -4);
                 closed = true;
             } else {
-                beta = tot[0] / gamma;
-                alpha = tot[0] / (tot[1] - beta * tot[0] / alpha);
-                gamma = tot[0];
-                first = false;
+                beta = sum[0] / gamma;
+                alpha = sum[0] / (sum[1] - beta * sum[0] / alpha);
+                gamma = sum[0];
             }
         }
-        if (closed) {
-            if (!shown) {
-                publish_x(step);
-                if (!barrier(false)) return false;
-            }
-            mode = SETUP;
+        if (!shown) {
+            publish_x(step);
+            if (!barrier(false)) return false;
         }
     }
     if (leader) {
+        atomicAdd(fine ? &ctl->iters_fine : &ctl->iters_coarse, iters_all);
+        atomicAdd(fine ? &ctl->solves_fine : &ctl->solves_coarse, (unsigned long long)nsteps);
+        atomicMax(&ctl->max_iters, iters_max);
+        atomicMax(&ctl->max_relres_bits, (unsigned long long)relres_max);
         trec[TR_ROUNDS] = nbar - nbar0;
         trec[TR_ITERS] = iters_all;
         if constexpr (TIMED) {
