@@ -695,6 +695,9 @@ struct QueueArgs {
     int kindB, nB, sB0, dirB;
     Shape shapeA, shapeB;
     int lagB;  // B's slice n goes after A's slice n + lagB along the sweep
+    // lanes ahead of the two kinds and behind them (kind < 0: none)
+    int headKind[2], headSlice[2], tailKind;
+    Shape headShape[2], tailShape;
 };
 
 struct PlanArgs {
@@ -748,6 +751,9 @@ __global__ void k_build_plan(PlanArgs P, Group *groups, Lane *lanes, int *wg_gro
     const QueueArgs &Q = P.Q;
     if (Q.ngroups > 0) {
         const int lane0 = lidx;
+        for (int k = 0; k < 2; ++k)
+            if (Q.headKind[k] >= 0)
+                put_lane(lanes + lidx++, Q.headKind[k], Q.headSlice[k], 0, Q.headShape[k]);
         // merge the two slice sequences by position along the sweep, B lagging
         // lagB slices behind A (both run in the same direction)
         int ia = 0, ib = 0;
@@ -761,6 +767,7 @@ __global__ void k_build_plan(PlanArgs P, Group *groups, Lane *lanes, int *wg_gro
             if (takeA) ++ia;
             else ++ib;
         }
+        if (Q.tailKind >= 0) put_lane(lanes + lidx++, Q.tailKind, 0, 0, Q.tailShape);
         for (int q = 0; q < Q.ngroups; ++q) {
             Group G;
             G.wg0 = w;
@@ -859,11 +866,12 @@ int res_min_wgs(int W, int HN, int deg, int rows_max, size_t lds_cap) {
 }
 
 // Plans a launch whose lanes are all resident: group counts and sizes and the
-// lanes' shapes. False if the lanes do not fit the grid.
+// lanes' shapes. False if the lanes do not fit the grid. one_queue: the sweeps
+// have no groups of their own, all lanes go through the shared queue.
 bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt_tuning &T,
                    int grid, int lds_cap_d, int sweep_wgs, const CoarseMesh *cm,
                    std::vector<int> &ngroups, std::vector<int> &nwg, std::vector<Shape> &shape,
-                   std::vector<Shape> &lead_shape, size_t &lds) {
+                   std::vector<Shape> &lead_shape, size_t &lds, bool &one_queue) {
     const int HN = C.ny + 1;
     const size_t cap = (size_t)lds_cap_d * sizeof(double);
     const int rows_max = std::max(2, T.resident_npt_max);
@@ -872,37 +880,45 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         if (kind == F_PRI || kind == F_ADJ) return deg_f;
         return C.coarse_iters > 0 ? 0 : deg_c;
     };
+    // the lane's degree, or the largest below it whose window fits
     auto fit = [&](int kind, int max_wg, Shape &s, int &n) {
-        return res_shape(C.W, HN, max_wg, deg_of(kind), rows_max, cap, s, n);
+        for (int deg = deg_of(kind); deg >= 0; --deg)
+            if (res_shape(C.W, HN, max_wg, deg, rows_max, cap, s, n)) return true;
+        return false;
     };
-    auto min_wgs = [&](int kind) { return res_min_wgs(C.W, HN, deg_of(kind), rows_max, cap); };
-    // the least workgroups that hold the grid for every kind of batched lane
-    int g_min = 0, nb = 0, lanes = 0, lat = 0;
-    for (size_t k = 0; k < plans.size(); ++k) {
-        const LanePlan &p = plans[k];
-        if (p.latency || p.count == 0) continue;
-        ++nb;
-        lanes += p.count;
-        if (is_cm_kind(p.kind)) continue;
-        const int g = min_wgs(p.kind);
-        if (g == 0 || g > grid) return false;
-        g_min = std::max(g_min, g);
-    }
+    auto min_wgs = [&](int kind, int deg) { return res_min_wgs(C.W, HN, deg, rows_max, cap); };
     lds = 0;
-    // sequential sweeps on groups of their own
+    one_queue = false;
+    // the least workgroups that hold the grid for every kind of batched lane
+    int g_min = 0, nb = 0, lanes = 0, lat = 0, fk = -1;
+    bool sweeps = false;
     for (size_t k = 0; k < plans.size(); ++k) {
         const LanePlan &p = plans[k];
         ngroups[k] = 0;
         nwg[k] = 1;
+        if (p.latency) sweeps |= p.count > 0;
+        if (p.latency || p.count == 0) continue;
+        ++nb;
+        lanes += p.count;
+        if (is_cm_kind(p.kind)) continue;
+        if (p.kind == F_PRI || p.kind == F_ADJ) fk = p.kind;
+        const int g = min_wgs(p.kind, deg_of(p.kind));
+        if (g == 0) return false;
+        g_min = std::max(g_min, g);
+    }
+    // sequential sweeps on groups of their own
+    bool own = true;
+    for (size_t k = 0; own && k < plans.size(); ++k) {
+        const LanePlan &p = plans[k];
         if (!p.latency || p.count == 0) continue;
         const int want = p.fixed_nwg > 0 ? p.fixed_nwg : std::min(sweep_wgs, grid / 4);
         int n = want;
         if (is_cm_kind(p.kind)) shape[k] = Shape{0, 0, 0, 0, 0};
-        else if (!fit(p.kind, std::max(want, min_wgs(p.kind)), shape[k], n)) return false;
-        if (p.lead_kind >= 0) {
+        else own = fit(p.kind, std::max(want, min_wgs(p.kind, deg_of(p.kind))), shape[k], n);
+        if (own && p.lead_kind >= 0) {
             int m = 0;
-            if (!fit(p.lead_kind, std::max(n, min_wgs(p.lead_kind)), lead_shape[k], m))
-                return false;
+            own = fit(p.lead_kind, std::max(n, min_wgs(p.lead_kind, deg_of(p.lead_kind))),
+                      lead_shape[k], m);
             n = std::max(n, m);
             lds = std::max(lds, res_lds_bytes(lead_shape[k], C.W, HN));
         }
@@ -911,9 +927,47 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         nwg[k] = n;
         lat += n * p.count;
     }
+    const bool share = T.shared_queue != 0;
     // the rest of the grid for the batched lanes, on groups of one size
     int avail = g_min > 0 ? (grid - lat) / g_min : nb;
-    if (avail < nb) return false;
+    if (!own || grid < lat) avail = 0;
+    // A grid so large that beside the sweep's group only one other is left: the
+    // sweep's workgroups, which mostly wait for that group's lanes, are better used
+    // for such lanes too, the sweep following as the queue's last lane. With 32
+    // slices of 16 steps the fine and batched coarse lanes are about four times the
+    // sweep's work, so two groups and then the sweep take 4/2 + 1 against 4; where
+    // two groups are left beside the sweep, 4/2 against 4/3 + 1.
+    if (share && sweeps && !cm && fk >= 0 && avail < 2) {
+        int g = 0;
+        for (int deg = deg_f; deg >= 1; --deg) {
+            g = min_wgs(fk, deg);
+            if (g > 0 && g <= grid) break;
+        }
+        const int G = g > 0 ? std::min(grid / g, lanes) : 0;
+        if (G > avail) {
+            one_queue = true;
+            const int gsz = grid / G;
+            lds = 0;
+            int used = 1;
+            for (size_t k = 0; k < plans.size(); ++k) {
+                const LanePlan &p = plans[k];
+                if (p.count == 0) continue;
+                int n = 1, m = 1;
+                if (!fit(p.kind, gsz, shape[k], n)) return false;
+                if (!fit(p.lead_kind >= 0 ? p.lead_kind : p.kind, gsz, lead_shape[k], m))
+                    return false;
+                lds = std::max(lds, std::max(res_lds_bytes(shape[k], C.W, HN),
+                                             res_lds_bytes(lead_shape[k], C.W, HN)));
+                used = std::max(used, std::max(n, m));
+            }
+            for (size_t k = 0; k < plans.size(); ++k) {
+                ngroups[k] = plans[k].kind == fk ? G : 0;
+                nwg[k] = used;
+            }
+            return true;
+        }
+    }
+    if (avail < 1 || (avail < nb && (!share || nb > 2))) return false;
     avail = std::min(avail, lanes);
     const int gsz = g_min > 0 ? std::max(g_min, (grid - lat) / std::max(1, avail)) : 1;
     int left = avail, kinds = nb;
@@ -927,6 +981,8 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         --kinds;
         int q = p.queues > 0 ? p.queues : (int)floor(avail * p.weight * p.count / wF);
         q = std::max(1, std::min(q, std::min(p.count, left - kinds)));
+        // (one group for two kinds: they share a queue)
+        q = std::min(q, left);
         ngroups[k] = q;
         left -= q;
         int n = 1;
@@ -972,11 +1028,12 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     std::vector<int> ngroups(plans.size()), per_group(plans.size()), nwg(plans.size());
     std::vector<Shape> shape(plans.size()), lead_shape(plans.size());
     size_t res_lds = 0;
+    bool one_queue = false;
     // checkpointed and multigrid lanes stream
     bool resident = T.resident != 0 && !C.gmg && !C.ckpt;
     if (resident)
         resident = plan_resident(C, plans, T, grid, lds_cap_d, sweep_wgs_res, cm, ngroups, nwg,
-                                 shape, lead_shape, res_lds);
+                                 shape, lead_shape, res_lds, one_queue);
     if (resident)
         for (size_t k = 0; k < plans.size(); ++k)
             per_group[k] = ngroups[k] > 0 ? (plans[k].count + ngroups[k] - 1) / ngroups[k] : 0;
@@ -1100,22 +1157,45 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
         }
         if (qa >= 0 && qb >= 0 && (nwg[qa] != nwg[qb] || plans[qa].dir != plans[qb].dir))
             qa = qb = -1;
-        if (qb < 0) qa = qb = -1;
+        if (qb < 0 && !one_queue) qa = qb = -1;
+    }
+    QueueArgs &Q = P.Q;
+    Q.headKind[0] = Q.headKind[1] = Q.tailKind = -1;
+    if (one_queue) {
+        // a cold sweep first, then the slice that the correction sweep's first step
+        // reads, the other lanes in its order, the correction sweep last: every lane
+        // waits on earlier ones only
+        for (size_t k = 0; k < plans.size(); ++k) {
+            const auto &p = plans[k];
+            if (!p.latency || p.count == 0) continue;
+            if (p.kind == COLD_PRI || p.kind == COLD_ADJ) {
+                Q.headKind[0] = p.kind;
+                Q.headSlice[0] = p.slice0;
+                Q.headShape[0] = shape[k];
+            } else {
+                Q.tailKind = p.kind;
+                Q.tailShape = shape[k];
+                Q.headKind[1] = p.lead_kind;
+                Q.headSlice[1] = p.lead_slice;
+                Q.headShape[1] = lead_shape[k];
+            }
+        }
     }
     if (qa >= 0) {
-        QueueArgs &Q = P.Q;
-        Q.ngroups = ngroups[qa] + ngroups[qb];
+        Q.ngroups = ngroups[qa] + (qb >= 0 ? ngroups[qb] : 0);
         Q.nwg = nwg[qa];
         Q.shapeA = shape[qa];
-        Q.shapeB = shape[qb];
         Q.kindA = plans[qa].kind;
         Q.nA = plans[qa].count;
         Q.sA0 = plans[qa].slice0;
         Q.dirA = plans[qa].dir;
-        Q.kindB = plans[qb].kind;
-        Q.nB = plans[qb].count;
-        Q.sB0 = plans[qb].slice0;
-        Q.dirB = plans[qb].dir;
+        if (qb >= 0) {
+            Q.shapeB = shape[qb];
+            Q.kindB = plans[qb].kind;
+            Q.nB = plans[qb].count;
+            Q.sB0 = plans[qb].slice0;
+            Q.dirB = plans[qb].dir;
+        }
         // a fine lane takes about as long as the sweep's next several steps:
         // queued a few slices ahead of the batched coarse steps, the last fine
         // lanes no longer hold up the sweep's last steps
@@ -1123,7 +1203,7 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     }
     for (size_t k = 0; k < plans.size(); ++k) {
         const auto &p = plans[k];
-        if (p.count == 0 || (int)k == qa || (int)k == qb) continue;
+        if (p.count == 0 || (int)k == qa || (int)k == qb || one_queue) continue;
         if (P.nruns >= 6) return PT_EINVAL;
         Run &R = P.run[P.nruns++];
         R.kind = p.kind;

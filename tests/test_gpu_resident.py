@@ -62,3 +62,29 @@ def test_restarts_near_round_off(gpu):
     print(e, g["status"], flush=True)
     assert g["status"]["status"] == -4
     assert max(e.values()) <= 1e-10
+
+
+@pytest.mark.parametrize("nx,ny,propagator", [(256, 230, 0), (300, 310, 0), (320, 288, 2)])
+@pytest.mark.parametrize("warm", [False, True])
+def test_grids_that_leave_one_group_beside_the_sweep(gpu, nx, ny, propagator, warm):
+    """Grids of which the device holds few groups (two window rows per thread make
+    them few already at these sizes): every lane in one queue with the sweeps first and
+    last, or one group for all fine and batched coarse lanes. dtau / h^2 <= 610, as above
+    condition numbers stay below 1e3."""
+    cfg = _cfg(nx=nx, ny=ny, n_steps=12, n_slices=3, t_final=0.018, propagator=propagator,
+               tuning=dict(resident_npt_max=2))
+    rho = density_uniform_noise(nx, ny, nx)
+    ref = run_oracle(cfg, rho)
+    guess = None
+    if warm:
+        guess = (ref["uT"], ref["utheta"], ref["lam"])
+        rho = np.clip(rho + 0.02, 0.0, 1.0)
+        ref = run_oracle(cfg, rho, guess)
+    g = run_gpu(cfg, rho, guess, with_status=True, with_trace=True)
+    e = compare(g, ref)
+    wgs = {r["kind"]: r["nwg"] for r in g["trace"]}
+    print(nx, ny, propagator, warm, e, wgs, g["status"], flush=True)
+    assert g["status"]["status"] == 0
+    if propagator == 0:
+        assert len(set(wgs.values())) == 1
+    assert max(e.values()) <= 1e-10
