@@ -349,7 +349,10 @@ int pt_filter_projection_backward(const pt_filter *f, const double *chi_fil,
  * a batched coarse step; a design's coarse sweep) are taken from two queues by
  * groups of workgroups: `sweep_groups` groups of `sweep_wgs` workgroups run
  * the sequential coarse sweeps, the rest of the grid is cut into groups of
- * `fine_wgs` workgroups for the fine and batched coarse lanes. */
+ * `fine_wgs` workgroups for the fine and batched coarse lanes. With exactly the
+ * built-in values (pt_batch_default_tuning) and designs that all fit on chip the
+ * library instead plans groups of a size for each class of designs, with vectors
+ * held in registers and a design's sweep last among its lanes. */
 typedef struct pt_batch_tuning {
     int32_t fine_wgs;      /* workgroups per fine-lane group, 1..1024                         */
     int32_t sweep_wgs;     /* workgroups per sweep group, 1..1024                             */

@@ -19,6 +19,7 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxGrid = 1024;         // workgroups of one engine launch
+constexpr int kMaxQueues = 8;          // lane queues of a launch
 constexpr int kMaxBatchGroups = 512;   // worker groups of a multi-design launch
 constexpr long long kGmgLdsBytes = 158 * 1024;  // dynamic LDS of the multigrid lanes
 
@@ -256,7 +257,7 @@ void carve_shared(Carver &c, SharedLayout &S, int n_designs, int max_lanes, int 
     S.wg_group = c.take(sizeof(int) * kMaxGrid);
     S.groups = c.take(sizeof(Group) * kMaxGroups);
     S.lanes = c.take(sizeof(Lane) * (size_t)max_lanes);
-    S.qhead = c.take(sizeof(unsigned) * 2);
+    S.qhead = c.take(sizeof(unsigned) * kMaxQueues);
     S.qslot = c.take(sizeof(int) * kMaxGroups);
     S.pool = c.take(sizeof(double) * (size_t)max_groups * kVecsPerLane * pool_stride);
     S.trace = c.take(sizeof(unsigned long long) * (size_t)max_lanes * trace_stride);
@@ -660,7 +661,7 @@ int reset_launch_state(void *ws, const SharedLayout &S, int n_designs, hipStream
     hipLaunchKernelGGL(k_fill_u32, dim3(64), dim3(256), 0, stream, at<unsigned>(ws, S.flags),
                        (size_t)kMaxFlags * n_designs, 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, at<unsigned>(ws, S.qhead),
-                       (size_t)2, 0u);
+                       (size_t)kMaxQueues, 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(64), dim3(256), 0, stream,
                        at<unsigned>(ws, S.trace), (size_t)S.max_lanes * S.trace_stride * 2, 0u);
     return launch_check();
@@ -1265,15 +1266,16 @@ bool overlaps(const void *a, size_t na, const void *b, size_t nb) {
 // Multi-design plan: worker groups sharing two lane queues
 // ---------------------------------------------------------------------------
 
-// Lanes of every design (blockIdx.x = design) in queue order. Queue 0 holds
-// the fine lanes F_n interleaved with the batched coarse lanes G(u^k_n) in the
-// order the design's sweep consumes them; queue 1 holds the cold sweeps of all
-// designs, then their correction sweeps. With designs in the order the host
-// chose, the lanes have a global order (all cold sweeps; then per design its
-// fine lanes and its correction sweep) that both queues follow and in which
-// every lane waits only on earlier lanes; as each queue hands out lanes in
-// that order, a waiting lane's producers have all been taken by running
-// groups, so the launch cannot deadlock.
+// Lanes of every design (blockIdx.x = design) in queue order: the fine lanes F_n
+// interleaved with the batched coarse lanes G(u^k_n) in the order the design's
+// sweep consumes them, the cold and the correction sweep where its plan puts them.
+// With the built-in shape a design's lanes are consecutive in one queue, the cold
+// sweep first and the correction sweep last. With a given shape the fine queue holds
+// the designs' fine and batched coarse lanes, the other one the cold sweeps of all
+// designs, then their correction sweeps. Either way the lanes have a global order
+// that every queue follows and in which every lane waits only on earlier lanes; as
+// each queue hands out lanes in that order, a waiting lane's producers have all been
+// taken by running groups, so the launch cannot deadlock.
 __global__ void k_build_lanes(const EngineDesc *__restrict__ D, Lane *lanes) {
     if (threadIdx.x != 0) return;
     const int d = blockIdx.x;
@@ -1303,38 +1305,30 @@ __global__ void k_build_lanes(const EngineDesc *__restrict__ D, Lane *lanes) {
     if (P.q1_sweep >= 0) put(P.q1_sweep, P.adjoint ? SWEEP_ADJ : SWEEP_PRI, 0, P.tile1);
 }
 
+// Worker groups of a multi-design launch: class c has n groups of wgs workgroups,
+// which take lanes lane0 .. lane0 + nlanes - 1 from queue c in order.
 struct GroupArgs {
-    int grid;
-    int n0, wgs0, lane0_0, nlanes0;  // queue 0 workers
-    int n1, wgs1, lane0_1, nlanes1;  // queue 1 workers
+    int grid, ncls;
+    struct {
+        int n, wgs, lane0, nlanes;
+    } cls[kMaxQueues];
 };
 
 __global__ void k_build_groups(GroupArgs A, Group *groups, int *wg_group) {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     int w = 0, gidx = 0;
-    // sweep workers first: their lanes are the longest sequential chains
-    for (int q = 0; q < A.n1; ++q, ++gidx) {
-        Group G;
-        G.wg0 = w;
-        G.nwg = A.wgs1;
-        G.lane0 = A.lane0_1;
-        G.nlanes = A.nlanes1;
-        G.vec = gidx;
-        G.queue = 1;
-        groups[gidx] = G;
-        for (int k = 0; k < A.wgs1; ++k) wg_group[w++] = gidx;
-    }
-    for (int q = 0; q < A.n0; ++q, ++gidx) {
-        Group G;
-        G.wg0 = w;
-        G.nwg = A.wgs0;
-        G.lane0 = A.lane0_0;
-        G.nlanes = A.nlanes0;
-        G.vec = gidx;
-        G.queue = 0;
-        groups[gidx] = G;
-        for (int k = 0; k < A.wgs0; ++k) wg_group[w++] = gidx;
-    }
+    for (int c = 0; c < A.ncls; ++c)
+        for (int q = 0; q < A.cls[c].n; ++q, ++gidx) {
+            Group G;
+            G.wg0 = w;
+            G.nwg = A.cls[c].wgs;
+            G.lane0 = A.cls[c].lane0;
+            G.nlanes = A.cls[c].nlanes;
+            G.vec = gidx;
+            G.queue = c;
+            groups[gidx] = G;
+            for (int k = 0; k < A.cls[c].wgs; ++k) wg_group[w++] = gidx;
+        }
     for (; w < A.grid; ++w) wg_group[w] = -1;
 }
 
@@ -1372,6 +1366,165 @@ bool batch_shape(const Consts &C, int wgs, int deg, int lds_cap_d, int (&out)[4]
     return true;
 }
 
+// Work of a design's pass in rounds of a resident group, and of its sweep alone:
+// about 11 rounds' time per fine step (8 to 10 and the set-up), 50 per coarse step.
+void batch_work(const EngineDesc &E, double &all, double &sweep) {
+    const double fine = 11.0 * E.C.Ntau * E.C.M, coarse = 50.0 * E.C.Ntau;
+    sweep = E.C.Ntau > 1 ? coarse : 0.0;
+    all = fine + sweep + (E.I.gk_lanes || E.I.cold ? coarse : 0.0);
+}
+
+// The built-in shape of a multi-design launch. Every design's lanes go through
+// one queue in an order in which each waits on earlier ones only: cold sweep,
+// fine and batched coarse lanes, correction sweep. Designs that need about as many
+// workgroups per group share a queue (a class), whose groups have the size of its
+// largest need (measured on twelve designs of 64^2 to 256^2 with 4 to 16 slices of
+// 16 steps: 500 ms a cycle on streaming groups of 2 and 16 workgroups, 60 ms here); the classes and their group counts are those of the least
+// estimated time. A round is bound by latency, not by its nodes, so a group of more
+// workgroups than a design needs is wasted on it; twelve designs of 64^2 to 256^2
+// with 4 to 16 slices take 2 to 36 workgroups each. False if a design fits no group.
+bool plan_batch(std::vector<EngineDesc> &hd, int grid, int cap_d, GroupArgs &A, size_t &lds) {
+    const int n = (int)hd.size();
+    const size_t cap = (size_t)cap_d * sizeof(double);
+    // us per round by window rows per thread (measured at 101^2 and 257^2 nodes)
+    constexpr double kRound[] = {6.0, 8.5, 10.5};
+    std::vector<int> need(n), best_of(n), idx(n);
+    std::vector<double> all(n), sweep(n);
+    for (int d = 0; d < n; ++d) {
+        if (hd[d].C.gmg) return false;
+        batch_work(hd[d], all[d], sweep[d]);
+    }
+    double best = INFINITY;
+    struct Cls {
+        int first, count, size, groups;
+    };
+    std::vector<Cls> best_cls;
+    std::vector<int> best_idx;
+    for (int v = 0; v < 3; ++v) {
+        bool fits = true;
+        for (int d = 0; d < n && fits; ++d) {
+            const Consts &C = hd[d].C;
+            const int f = res_min_wgs(C.W, C.ny + 1, kBatchDegFine, kResRowChoices[v], cap);
+            const int c = res_min_wgs(C.W, C.ny + 1, kBatchDegCoarse, kResRowChoices[v], cap);
+            need[d] = std::max(f, c);
+            fits = f > 0 && c > 0 && need[d] <= grid;
+        }
+        if (!fits) continue;
+        std::iota(idx.begin(), idx.end(), 0);
+        std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return need[a] > need[b]; });
+        // classes are runs of idx: split, one cut more at a time, where it saves most
+        // workgroup time
+        std::vector<int> cut{0, n};
+        for (int K = 1; K <= std::min(n, kMaxQueues); ++K) {
+            if (K > 1) {
+                double gain = 0.0;
+                int at_ = -1;
+                for (size_t c = 0; c + 1 < cut.size(); ++c) {
+                    double tail = 0.0;
+                    for (int i = cut[c + 1] - 1; i > cut[c]; --i) {
+                        tail += all[idx[i]];
+                        const double gn = tail * (need[idx[cut[c]]] - need[idx[i]]);
+                        if (gn > gain) {
+                            gain = gn;
+                            at_ = i;
+                        }
+                    }
+                }
+                if (at_ < 0) break;
+                cut.insert(std::upper_bound(cut.begin(), cut.end(), at_), at_);
+            }
+            std::vector<Cls> cls;
+            std::vector<double> w, s;
+            std::vector<int> most;
+            int least = 0;
+            for (int c = 0; c < K; ++c) {
+                Cls k{cut[c], cut[c + 1] - cut[c], need[idx[cut[c]]], 1};
+                double wa = 0.0, sw = 0.0;
+                int lanes = 0;
+                for (int i = k.first; i < k.first + k.count; ++i) {
+                    wa += all[idx[i]];
+                    sw = std::max(sw, sweep[idx[i]]);
+                    lanes += hd[idx[i]].C.Ntau * 2;
+                }
+                cls.push_back(k);
+                w.push_back(wa);
+                s.push_back(sw);
+                most.push_back(lanes);
+                least += k.size;
+            }
+            if (least > grid) continue;
+            // a class's time: its work shared by its groups, the last sweep alone
+            auto time = [&](int c, int g) { return (w[c] - s[c]) / g + s[c]; };
+            for (int left = grid - least;;) {
+                int worst = 0;
+                for (int c = 1; c < K; ++c)
+                    if (time(c, cls[c].groups) > time(worst, cls[worst].groups)) worst = c;
+                if (cls[worst].size > left || cls[worst].groups >= most[worst] ||
+                    s[worst] >= 0.9 * time(worst, cls[worst].groups)) {
+                    const double t = kRound[v] * time(worst, cls[worst].groups);
+                    if (t < best) {
+                        best = t;
+                        best_cls = cls;
+                        best_idx = idx;
+                    }
+                    break;
+                }
+                left -= cls[worst].size;
+                ++cls[worst].groups;
+            }
+        }
+    }
+    if (!(best < INFINITY)) return false;
+    lds = 0;
+    A.ncls = (int)best_cls.size();
+    int lane = 0;
+    for (int c = 0; c < A.ncls; ++c) {
+        const Cls &k = best_cls[c];
+        A.cls[c] = {k.groups, k.size, lane, 0};
+        A.grid += k.groups * k.size;
+        // the designs with the most work first
+        std::vector<int> in(best_idx.begin() + k.first, best_idx.begin() + k.first + k.count);
+        std::stable_sort(in.begin(), in.end(), [&](int a, int b) { return all[a] > all[b]; });
+        for (int d : in) {
+            EngineDesc &E = hd[d];
+            DesignPlan &P = E.plan;
+            const int Ntau = E.C.Ntau;
+            if (!batch_shape(E.C, k.size, kBatchDegFine, cap_d, P.fine) ||
+                !batch_shape(E.C, k.size, kBatchDegCoarse, cap_d, P.gk))
+                return false;
+            memcpy(P.sweep, P.gk, sizeof(P.gk));
+            for (const auto *v : {P.fine, P.gk})
+                lds = std::max(lds, res_lds_bytes(Shape{0, v[0], v[1], v[2], v[3]}, E.C.W,
+                                                  E.C.ny + 1));
+            P.tile0 = P.tile1 = 0;
+            P.q1_cold = E.I.cold ? lane++ : -1;
+            P.q0_lane0 = lane;
+            P.q0_count = Ntau + (E.I.gk_lanes ? Ntau - 1 : 0);
+            lane += P.q0_count;
+            P.q1_sweep = Ntau > 1 ? lane++ : -1;
+        }
+        A.cls[c].nlanes = lane - A.cls[c].lane0;
+    }
+    return true;
+}
+
+// Uploads the designs, builds lanes and groups and launches the engine.
+int launch_batch(std::vector<EngineDesc> &hd, const Engine &K, const GroupArgs &A,
+                 size_t lds_bytes, bool adjoint, const Device &dev, void *ws,
+                 const BatchLayout &Lay, hipStream_t stream) {
+    const int n = (int)hd.size();
+    for (auto &E : hd) E.plan.adjoint = adjoint ? 1 : 0;
+    EngineDesc *D = at<EngineDesc>(ws, Lay.s.desc);
+    PT_TRY(upload_descs(hd, D, stream));
+    hipLaunchKernelGGL(k_build_lanes, dim3(n), dim3(64), 0, stream, D, at<Lane>(ws, Lay.s.lanes));
+    hipLaunchKernelGGL(k_build_groups, dim3(1), dim3(64), 0, stream, A,
+                       at<Group>(ws, Lay.s.groups), at<int>(ws, Lay.s.wg_group));
+    PT_TRY(launch_check());
+    PT_TRY(reset_launch_state(ws, Lay.s, n, stream));
+    const Launch X = make_launch(ws, Lay.s, hd[0].B.ctl, hd[0].C.timeout_ticks);
+    return launch_engine(K, D, nullptr, X, A.grid, lds_bytes, dev, stream);
+}
+
 // Plans and runs one multi-design engine launch. `hd` holds the designs'
 // descriptors (C, B, I set); their DesignPlan is filled here and the
 // descriptors are uploaded.
@@ -1382,6 +1535,16 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
     PT_TRY(device_info(dev));
     const bool fp32 = hd[0].C.fp32 != 0;
     const int cap_d = lds_cap_doubles(dev);
+    // the built-in shape: one queue per class of designs where all of them fit
+    const pt_batch_tuning dflt = default_tuning(n);
+    if (memcmp(&T, &dflt, sizeof(T)) == 0) {
+        const int grid = std::min(dev.cus, kMaxGrid);
+        GroupArgs A{};
+        size_t lds = 0;
+        if (plan_batch(hd, grid, cap_d, A, lds) && lds <= (size_t)dev.lds_max)
+            return launch_batch(hd, Engine{true, fp32, true, false, false}, A, lds, adjoint, dev,
+                                ws, Lay, stream);
+    }
     bool resident = T.resident != 0;
     // tiles and LDS of every design on both kinds of worker
     size_t lds_d = 0, res_lds = 0;
@@ -1414,7 +1577,6 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
                     res_lds = std::max(res_lds, res_lds_bytes(Shape{0, v[0], v[1], v[2], v[3]},
                                                               C.W, C.ny + 1));
         }
-        E.plan.adjoint = adjoint ? 1 : 0;
         if (C.gmg && (C.gmg_chunk < 256 || C.gmg_chunk_init < 256)) return PT_EINVAL;
         lds_d = std::max(lds_d, C.gmg ? (gmg_lds_bytes(C) + 7) / 8
                                       : engine_lds_doubles(std::max(t0, t1), C.W));
@@ -1450,27 +1612,17 @@ int run_batched_engine(std::vector<EngineDesc> &hd, const pt_batch_tuning &T, bo
     int grid = std::min(cap, kMaxGrid);
     if (T.grid > 0) grid = std::min(grid, T.grid);
     GroupArgs A{};
-    A.n1 = q1 > 0 ? std::min(T.sweep_groups, q1) : 0;
-    A.wgs1 = T.sweep_wgs;
-    A.lane0_1 = q0;
-    A.nlanes1 = q1;
-    A.wgs0 = T.fine_wgs;
-    A.lane0_0 = 0;
-    A.nlanes0 = q0;
-    const int left = grid - A.n1 * A.wgs1;
-    if (left < A.wgs0) return PT_EINVAL;
-    A.n0 = std::min(std::min(left / A.wgs0, q0), kMaxBatchGroups - A.n1);
-    if (A.n0 < 1) return PT_EINVAL;
-    A.grid = A.n1 * A.wgs1 + A.n0 * A.wgs0;
-    EngineDesc *D = at<EngineDesc>(ws, Lay.s.desc);
-    PT_TRY(upload_descs(hd, D, stream));
-    hipLaunchKernelGGL(k_build_lanes, dim3(n), dim3(64), 0, stream, D, at<Lane>(ws, Lay.s.lanes));
-    hipLaunchKernelGGL(k_build_groups, dim3(1), dim3(64), 0, stream, A,
-                       at<Group>(ws, Lay.s.groups), at<int>(ws, Lay.s.wg_group));
-    PT_TRY(launch_check());
-    PT_TRY(reset_launch_state(ws, Lay.s, n, stream));
-    const Launch X = make_launch(ws, Lay.s, hd[0].B.ctl, hd[0].C.timeout_ticks);
-    return launch_engine(K, D, nullptr, X, A.grid, lds_bytes, dev, stream);
+    // sweep workers first: their lanes are the longest sequential chains
+    const int n1 = q1 > 0 ? std::min(T.sweep_groups, q1) : 0;
+    A.ncls = 2;
+    A.cls[0] = {n1, T.sweep_wgs, q0, q1};
+    const int left = grid - n1 * T.sweep_wgs;
+    if (left < T.fine_wgs) return PT_EINVAL;
+    const int n0 = std::min(std::min(left / T.fine_wgs, q0), kMaxBatchGroups - n1);
+    if (n0 < 1) return PT_EINVAL;
+    A.cls[1] = {n0, T.fine_wgs, 0, q0};
+    A.grid = n1 * T.sweep_wgs + n0 * T.fine_wgs;
+    return launch_batch(hd, K, A, lds_bytes, adjoint, dev, ws, Lay, stream);
 }
 
 bool valid_batch(int n, const pt_problem *probs) {

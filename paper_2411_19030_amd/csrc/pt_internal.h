@@ -230,7 +230,7 @@ struct Launch {
     const Lane *lanes;     // [n_lanes]
     unsigned *bar;         // [kMaxGroups][kBarParts][kBarLine] group barrier counters
     double *partials;      // [kMaxGroups][2][kMaxGroup][4]
-    unsigned *qhead;       // [2] next untaken position of each shared queue
+    unsigned *qhead;       // [kMaxQueues] next untaken position of each shared queue
     int *qslot;            // [kMaxGroups] lane position a group leader took
     unsigned long long *trace;  // per-lane record [n_lanes][trace_stride]
     int trace_stride;           // TR_HDR words + one timestamp per step

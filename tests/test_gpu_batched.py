@@ -109,6 +109,16 @@ def test_batched_worker_shapes(gpu, tuning):
     _check_batch(gpu, shapes, 1e-10, 1e-10, tuning=tuning, cg_rtol=1e-13, max_iter=20000)
 
 
+@pytest.mark.parametrize("count", [2, 9])
+def test_batched_classes_of_sizes(gpu, count):
+    """The built-in shape puts designs of unequal size into classes with groups of
+    their own: small designs alone, with larger ones, one without a sweep, and more
+    designs than classes. Bar as above (cg_rtol 1e-13)."""
+    shapes = [(127, 96, 12, 3), (12, 9, 16, 4), (60, 75, 12, 4), (64, 64, 8, 2), (90, 30, 9, 3),
+              (30, 30, 10, 1), (110, 50, 12, 2), (48, 40, 12, 6), (100, 90, 10, 5)]
+    _check_batch(gpu, shapes[:count], 1e-10, 1e-10, cg_rtol=1e-13, max_iter=20000)
+
+
 def test_batched_resident_mode(gpu):
     """Vectors in registers: every tile of every design must fit one workgroup."""
     shapes = [(16, 16, 32, 4), (24, 12, 30, 5), (32, 32, 64, 8), (40, 24, 48, 6)]
