@@ -1378,11 +1378,11 @@ void batch_work(const EngineDesc &E, double &all, double &sweep) {
 // one queue in an order in which each waits on earlier ones only: cold sweep,
 // fine and batched coarse lanes, correction sweep. Designs that need about as many
 // workgroups per group share a queue (a class), whose groups have the size of its
-// largest need (measured on twelve designs of 64^2 to 256^2 with 4 to 16 slices of
-// 16 steps: 500 ms a cycle on streaming groups of 2 and 16 workgroups, 60 ms here); the classes and their group counts are those of the least
-// estimated time. A round is bound by latency, not by its nodes, so a group of more
-// workgroups than a design needs is wasted on it; twelve designs of 64^2 to 256^2
-// with 4 to 16 slices take 2 to 36 workgroups each. False if a design fits no group.
+// largest need; the classes and their group counts are those of the least estimated
+// time. A round is bound by latency, not by its nodes, so a group of more workgroups
+// than a design needs is wasted on it: twelve designs of 64^2 to 256^2 with 4 to 16
+// slices need 2 to 36 each (500 ms a cycle on streaming groups of 2 and 16
+// workgroups, 60 ms here). False if a design fits no group.
 bool plan_batch(std::vector<EngineDesc> &hd, int grid, int cap_d, GroupArgs &A, size_t &lds) {
     const int n = (int)hd.size();
     const size_t cap = (size_t)cap_d * sizeof(double);

@@ -57,6 +57,58 @@ def test_filter_projection_against_oracle(gpu, nx, ny, r, beta, eta):
     assert max(e) <= 1e-13
 
 
+# around the edges of a block's tile (64 columns; 4 waves of 8 or 16 rows) and of
+# the pieces its rows are staged in, windows wider or higher than the grid, the
+# 16-row form (at least 200 blocks) and, at r = 0.8, a window of one thread per element
+EDGES = [(63, 31, 0.05), (64, 32, 0.05), (65, 33, 0.05), (1, 70, 0.2), (130, 1, 0.1),
+         (128, 64, 0.3), (200, 20, 0.9), (300, 12, 0.8), (1600, 520, 0.002), (512, 1600, 0.002)]
+
+
+def _by_shifts(nx, ny, r, x):
+    """sum_i w_ei x_i and W_e of every element, one shift of the grid at a time."""
+    x = x.reshape(ny, nx)
+    s, W = np.zeros((ny, nx)), np.zeros((ny, nx))
+    Rx, Ry = min(int(np.floor(r * nx)), nx - 1), min(int(np.floor(r * ny)), ny - 1)
+    for dj in range(-Ry, Ry + 1):
+        for di in range(-Rx, Rx + 1):
+            w = r - np.hypot(di / nx, dj / ny)
+            if w <= 0.0:
+                continue
+            to = (slice(max(0, -dj), ny - max(0, dj)), slice(max(0, -di), nx - max(0, di)))
+            fr = (slice(max(0, dj), ny - max(0, -dj)), slice(max(0, di), nx - max(0, -di)))
+            s[to] += w * x[fr]
+            W[to] += w
+    return s.reshape(-1), W.reshape(-1)
+
+
+@pytest.mark.parametrize("nx,ny,r", EDGES)
+def test_tile_edges(gpu, nx, ny, r):
+    rng = np.random.default_rng(nx * 1000 + ny)
+    chi = rng.uniform(0.0, 1.0, nx * ny)
+    grad = rng.standard_normal(nx * ny)
+    fil, phys, gc = _gpu(nx, ny, r, 8.0, 0.5, chi, grad)
+    num, W = _by_shifts(nx, ny, r, chi)
+    o_fil = num / W
+    o_phys = O.design.projection(o_fil, 8.0, 0.5)
+    o_gc, _ = _by_shifts(nx, ny, r, O.design.projection_deriv(o_fil, 8.0, 0.5) * grad / W)
+    e = (_rel(fil, o_fil), _rel(phys, o_phys), _rel(gc, o_gc))
+    print(nx, ny, r, e, flush=True)
+    assert max(e) <= 1e-13
+
+
+def test_values_that_are_not_finite_stay_in_their_window(gpu):
+    """A NaN and an infinity reach exactly the elements whose window holds them."""
+    nx, ny, r = 150, 90, 0.06
+    chi = np.random.default_rng(2).uniform(0.0, 1.0, nx * ny).reshape(ny, nx)
+    Rx, Ry = int(r * nx), int(r * ny)
+    chi[40, 70], chi[2, 149] = np.nan, np.inf
+    fil, _, _ = _gpu(nx, ny, r, 0.0, 0.5, chi.reshape(-1), chi.reshape(-1))
+    hit = np.zeros((ny, nx), dtype=bool)
+    hit[40 - Ry:41 + Ry, 70 - Rx:71 + Rx] = True
+    hit[:3 + Ry, 149 - Rx:] = True
+    assert np.array_equal(~np.isfinite(fil.reshape(ny, nx)), hit)
+
+
 def test_identity_below_one_element(gpu):
     """Only the element itself has a positive weight: chi_fil = (r chi) / r,
     within one rounding of chi."""
