@@ -27,6 +27,10 @@
 // After a correction launch, k_cm_correct forms the corrected fine states
 // F_n + P(Gn[n] - Gk[n]) and k_cm_sens the coarse-correction sensitivities.
 //
+// This file runs them in streaming launches (checkpointed or large grids);
+// launches of resident lanes run them as resident lanes of the coarse mesh
+// (pt_resident.hip).
+//
 // Every solve is Jacobi PCG in the single-reduction form of Chronopoulos and
 // Gear, one group barrier per iteration, on the assembled 9-point rows of
 // C_c/dtau + K_c. The group's workgroups own contiguous coarse-node tiles; each

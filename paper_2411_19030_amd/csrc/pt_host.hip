@@ -879,15 +879,29 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
     const int deg_f = 3, deg_c = 4;
     auto deg_of = [&](int kind) {
         if (kind == F_PRI || kind == F_ADJ) return deg_f;
+        // Coarse-mesh solves are better conditioned: at degree 4 those of 17^2 nodes
+        // take 6 rounds, no more than the fine ones, so that an iteration cap that
+        // just passes the fine solves would no longer report the coarse ones. Small
+        // meshes keep degree 1 (such a pass is bound by its fine lanes), larger ones
+        // 3 (129^2 nodes at degree 4: 22 rounds against 9).
+        if (is_cm_kind(kind)) return (C.nx / 2) * (C.ny / 2) <= 48 * 48 ? 1 : deg_f;
         return C.coarse_iters > 0 ? 0 : deg_c;
     };
     // the lane's degree, or the largest below it whose window fits
+    auto rows_of = [&](int kind) { return is_cm_kind(kind) ? C.ny / 2 + 1 : HN; };
+    auto width_of = [&](int kind) { return is_cm_kind(kind) ? C.nx / 2 + 1 : C.W; };
     auto fit = [&](int kind, int max_wg, Shape &s, int &n) {
         for (int deg = deg_of(kind); deg >= 0; --deg)
-            if (res_shape(C.W, HN, max_wg, deg, rows_max, cap, s, n)) return true;
+            if (res_shape(width_of(kind), rows_of(kind), max_wg, deg, rows_max, cap, s, n))
+                return true;
         return false;
     };
-    auto min_wgs = [&](int kind, int deg) { return res_min_wgs(C.W, HN, deg, rows_max, cap); };
+    auto min_wgs = [&](int kind, int deg) {
+        return res_min_wgs(width_of(kind), rows_of(kind), deg, rows_max, cap);
+    };
+    auto lds_of = [&](int kind, const Shape &s) {
+        return res_lds_bytes(s, width_of(kind), rows_of(kind));
+    };
     lds = 0;
     one_queue = false;
     // the least workgroups that hold the grid for every kind of batched lane
@@ -901,7 +915,6 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         if (p.latency || p.count == 0) continue;
         ++nb;
         lanes += p.count;
-        if (is_cm_kind(p.kind)) continue;
         if (p.kind == F_PRI || p.kind == F_ADJ) fk = p.kind;
         const int g = min_wgs(p.kind, deg_of(p.kind));
         if (g == 0) return false;
@@ -914,16 +927,15 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         if (!p.latency || p.count == 0) continue;
         const int want = p.fixed_nwg > 0 ? p.fixed_nwg : std::min(sweep_wgs, grid / 4);
         int n = want;
-        if (is_cm_kind(p.kind)) shape[k] = Shape{0, 0, 0, 0, 0};
-        else own = fit(p.kind, std::max(want, min_wgs(p.kind, deg_of(p.kind))), shape[k], n);
+        own = fit(p.kind, std::max(want, min_wgs(p.kind, deg_of(p.kind))), shape[k], n);
         if (own && p.lead_kind >= 0) {
             int m = 0;
             own = fit(p.lead_kind, std::max(n, min_wgs(p.lead_kind, deg_of(p.lead_kind))),
                       lead_shape[k], m);
             n = std::max(n, m);
-            lds = std::max(lds, res_lds_bytes(lead_shape[k], C.W, HN));
+            lds = std::max(lds, lds_of(p.lead_kind, lead_shape[k]));
         }
-        if (!is_cm_kind(p.kind)) lds = std::max(lds, res_lds_bytes(shape[k], C.W, HN));
+        lds = std::max(lds, lds_of(p.kind, shape[k]));
         ngroups[k] = p.count;
         nwg[k] = n;
         lat += n * p.count;
@@ -968,7 +980,7 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
             return true;
         }
     }
-    if (avail < 1 || (avail < nb && (!share || nb > 2))) return false;
+    if (!own || (nb > 0 && (avail < 1 || (avail < nb && (!share || nb > 2))))) return false;
     avail = std::min(avail, lanes);
     const int gsz = g_min > 0 ? std::max(g_min, (grid - lat) / std::max(1, avail)) : 1;
     int left = avail, kinds = nb;
@@ -987,11 +999,8 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         ngroups[k] = q;
         left -= q;
         int n = 1;
-        if (is_cm_kind(p.kind)) shape[k] = Shape{0, 0, 0, 0, 0};
-        else {
-            if (!fit(p.kind, gsz, shape[k], n)) return false;
-            lds = std::max(lds, res_lds_bytes(shape[k], C.W, HN));
-        }
+        if (!fit(p.kind, gsz, shape[k], n)) return false;
+        lds = std::max(lds, lds_of(p.kind, shape[k]));
         used_max = std::max(used_max, n);
     }
     for (size_t k = 0; k < plans.size(); ++k)
@@ -1133,7 +1142,7 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     size_t lds_bytes =
         resident ? res_lds
                  : C.gmg ? gmg_lds_bytes(C) : engine_lds_doubles(max_tile, C.W) * sizeof(double);
-    if (cm) {
+    if (cm && !resident) {
         // a coarse-mesh lane stages two windows of its coarse tile and halo
         for (size_t k = 0; k < plans.size(); ++k)
             if (is_cm_kind(plans[k].kind) && plans[k].count > 0) {

@@ -123,8 +123,12 @@ __device__ __forceinline__ double res_omega(double lo, double hi, int deg, int i
 // memory would be generic ones.)
 typedef __attribute__((address_space(1))) double gdouble;
 typedef __attribute__((address_space(1))) char gchar;
+typedef __attribute__((address_space(1))) unsigned char gbyte;
 __device__ __forceinline__ gdouble *nd(const double *p, unsigned n) {
     return (gdouble *)((gchar *)p + n * 8u);
+}
+__device__ __forceinline__ const gbyte *ndb(const unsigned char *p, unsigned n) {
+    return reinterpret_cast<const gbyte *>(reinterpret_cast<uintptr_t>(p)) + n;
 }
 __device__ __forceinline__ double ldg(const double *p, unsigned n) {
     return __hip_atomic_load(nd(p, n), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -264,29 +268,18 @@ struct ResGeo {
             if (rim_id[i] >= 0) lds[zb + rim_cell[i]] = vr[i];
     }
     // The operator at the thread's nodes from the element values: gap k lies below
-    // row k, its elements left and right of the column are (gx - 1, gy0 + k - 1) and
-    // (gx, gy0 + k - 1); cc is the diagonal.
+    // row k, its elements left and right of the column have mass ml, mr (c hx hy/36
+    // over the step) and stiffness kl, kr (k/6); cc is the diagonal.
     template <int NR>
-    __device__ __forceinline__ void coefs(const Consts &C, const Bufs &B, bool fine,
-                                          ResCoef<NR> &Q, double (&cc)[NR]) const {
-        const double ms = fine ? C.inv_dt : C.inv_dtau;
-        const bool inx = act && gx >= 0 && gx < W;
-        double ml[NR + 1], mr[NR + 1], kl[NR + 1], kr[NR + 1];
-#pragma unroll
-        for (int k = 0; k <= NR; ++k) {
-            const int ey = gy0 + k;  // padded element row
-            const bool in = inx && ey >= 0 && ey <= C.ny + 1;
-            // (element 0 is padding: its values are 0)
-            const unsigned e = in ? (unsigned)(ey * C.EW + gx) : 0u, d = in ? 1u : 0u;
-            ml[k] = *nd(B.cm, e);
-            mr[k] = *nd(B.cm, e + d);
-            kl[k] = *nd(B.kq, e);
-            kr[k] = *nd(B.kq, e + d);
-        }
+    static __device__ __forceinline__ void assemble(const Consts &C, const double (&ml)[NR + 1],
+                                                    const double (&mr)[NR + 1],
+                                                    const double (&kl)[NR + 1],
+                                                    const double (&kr)[NR + 1], ResCoef<NR> &Q,
+                                                    double (&cc)[NR]) {
         double sl = 0.0, sr = 0.0, xl = 0.0, xr = 0.0;
 #pragma unroll
         for (int k = 0; k <= NR; ++k) {
-            const double a = ml[k] * ms, b = mr[k] * ms;
+            const double a = ml[k], b = mr[k];
             Q.dl[k] = a + C.e_d * kl[k];
             Q.dr[k] = b + C.e_d * kr[k];
             Q.nn[k] = 2.0 * (a + b) + C.e_y * (kl[k] + kr[k]);
@@ -301,6 +294,73 @@ struct ResGeo {
             sr = nsr;
             xl = nxl;
             xr = nxr;
+        }
+    }
+    // from the padded element values: elements (gx - 1, gy0 + k - 1), (gx, gy0 + k - 1)
+    template <int NR>
+    __device__ __forceinline__ void coefs(const Consts &C, const Bufs &B, bool fine,
+                                          ResCoef<NR> &Q, double (&cc)[NR]) const {
+        const double ms = fine ? C.inv_dt : C.inv_dtau;
+        const bool inx = act && gx >= 0 && gx < W;
+        double ml[NR + 1], mr[NR + 1], kl[NR + 1], kr[NR + 1];
+#pragma unroll
+        for (int k = 0; k <= NR; ++k) {
+            const int ey = gy0 + k;  // padded element row
+            const bool in = inx && ey >= 0 && ey <= C.ny + 1;
+            // (element 0 is padding: its values are 0)
+            const unsigned e = in ? (unsigned)(ey * C.EW + gx) : 0u, d = in ? 1u : 0u;
+            ml[k] = *nd(B.cm, e) * ms;
+            mr[k] = *nd(B.cm, e + d) * ms;
+            kl[k] = *nd(B.kq, e);
+            kr[k] = *nd(B.kq, e + d);
+        }
+        assemble<NR>(C, ml, mr, kl, kr, Q, cc);
+    }
+
+    // ---- the coarse mesh (W nodes per row as the window's grid) --------------------
+    // masses over dtau of the elements around the thread's nodes
+    template <int NR>
+    __device__ __forceinline__ void cm_mass(const Consts &C, const CoarseMesh &M,
+                                            double (&ml)[NR + 1], double (&mr)[NR + 1]) const {
+        const double ms = 4.0 * C.cm_unit * C.inv_dtau;
+        cm_elements<NR>(M, M.cE, ms, ml, mr);
+    }
+    template <int NR>
+    __device__ __forceinline__ void cm_elements(const CoarseMesh &M, const double *v, double f,
+                                                double (&l)[NR + 1], double (&r)[NR + 1]) const {
+        const bool inl = act && gx >= 1 && gx <= M.nxc, inr = act && gx >= 0 && gx < M.nxc;
+#pragma unroll
+        for (int k = 0; k <= NR; ++k) {
+            const int ey = gy0 + k - 1;
+            const bool in = ey >= 0 && ey < M.nyc;
+            const double a = *nd(v, in && inl ? (unsigned)(ey * M.nxc + gx - 1) : 0u);
+            const double b = *nd(v, in && inr ? (unsigned)(ey * M.nxc + gx) : 0u);
+            l[k] = in && inl ? a * f : 0.0;
+            r[k] = in && inr ? b * f : 0.0;
+        }
+    }
+    template <int NR>
+    __device__ __forceinline__ void cm_coefs(const Consts &C, const CoarseMesh &M, ResCoef<NR> &Q,
+                                             double (&cc)[NR]) const {
+        double ml[NR + 1], mr[NR + 1], kl[NR + 1], kr[NR + 1];
+        cm_mass<NR>(C, M, ml, mr);
+        cm_elements<NR>(M, M.kE, 1.0 / 6.0, kl, kr);
+        assemble<NR>(C, ml, mr, kl, kr, Q, cc);
+    }
+    // a fine row of values at the fine nodes of the thread's nodes in m, of the rim
+    template <int NR>
+    __device__ __forceinline__ void load_fine(const double *row, int Wf, unsigned m,
+                                              double (&v)[NR]) const {
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            v[k] = ldg(row, is(m, k) ? (unsigned)(2 * ((gy0 + k) * Wf + gx)) : 0u);
+    }
+    __device__ __forceinline__ void load_rim_fine(const double *row, int Wf,
+                                                  double (&v)[kRim]) const {
+#pragma unroll
+        for (int i = 0; i < kRim; ++i) {
+            const int j = rim_id[i] >= 0 ? rim_id[i] / W : 0, c = rim_id[i] - j * W;
+            v[i] = ldg(row, rim_id[i] >= 0 ? (unsigned)(2 * (j * Wf + c)) : 0u);
         }
     }
 };
@@ -340,6 +400,34 @@ __device__ __forceinline__ const double *res_b(const double *gv0, size_t gvs, in
 }
 __device__ __forceinline__ const double *res_x(const double *gv0, size_t gvs, int j) {
     return gv0 + (size_t)(V_S0 - V_R0 + (j & 3)) * gvs;
+}
+
+// bv = (M v) + bv at the thread's live nodes, 0 elsewhere: M the masses ml, mr of the
+// elements around them, v the operand window whose cell below the first node is z.
+template <int NR>
+__device__ __forceinline__ void res_mass(const ResGeo &g, int z, const double (&ml)[NR + 1],
+                                         const double (&mr)[NR + 1], double (&bv)[NR]) {
+    extern __shared__ double lds[];
+    const int sz = g.sz;
+    double l0 = lds[z - 1], c0 = lds[z], r0 = lds[z + 1];
+    z += sz;
+    double l1 = lds[z - 1], c1 = lds[z], r1 = lds[z + 1];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        z += sz;
+        const double l2 = lds[z - 1], c2 = lds[z], r2 = lds[z + 1];
+        const double ml0 = ml[k], mr0 = mr[k], ml1 = ml[k + 1], mr1 = mr[k + 1];
+        double m = 4.0 * ((ml0 + mr0) + (ml1 + mr1)) * c1;
+        m += 2.0 * ((mr0 + mr1) * r1 + (ml0 + ml1) * l1 + (ml1 + mr1) * c2 + (ml0 + mr0) * c0);
+        m += mr1 * r2 + ml1 * l2 + mr0 * r0 + ml0 * l0;
+        bv[k] = ResGeo::is(g.live, k) ? m + bv[k] : 0.0;
+        l0 = l1;
+        c0 = c1;
+        r0 = r1;
+        l1 = l2;
+        c1 = c2;
+        r1 = r2;
+    }
 }
 
 // The set-up: true residual and outputs of the finished solve
@@ -563,7 +651,7 @@ __device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, cons
         {
             // + (C/delta) tp on the window
             const double ms = fine ? C.inv_dt : C.inv_dtau;
-            int z = (prev && !sweep ? 0 : zlen) + cell0;
+            const int z = (prev && !sweep ? 0 : zlen) + cell0;
             double ml[NR + 1], mr[NR + 1];
             if (I.has_dc) {
                 const bool inx = g.act && g.gx >= 0 && g.gx < W;
@@ -585,26 +673,7 @@ __device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, cons
                     mr[k] = in && g.gx < C.nx ? m : 0.0;
                 }
             }
-            double l0 = lds[z - 1], c0 = lds[z], r0 = lds[z + 1];
-            z += sz;
-            double l1 = lds[z - 1], c1 = lds[z], r1 = lds[z + 1];
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                z += sz;
-                const double l2 = lds[z - 1], c2 = lds[z], r2 = lds[z + 1];
-                const double ml0 = ml[k], mr0 = mr[k], ml1 = ml[k + 1], mr1 = mr[k + 1];
-                double m = 4.0 * ((ml0 + mr0) + (ml1 + mr1)) * c1;
-                m += 2.0 * ((mr0 + mr1) * r1 + (ml0 + ml1) * l1 + (ml1 + mr1) * c2 +
-                            (ml0 + mr0) * c0);
-                m += mr1 * r2 + ml1 * l2 + mr0 * r0 + ml0 * l0;
-                bv[k] = is(g.live, k) ? m + bv[k] : 0.0;
-                l0 = l1;
-                c0 = c1;
-                r0 = r1;
-                l1 = l2;
-                c1 = c2;
-                r1 = r2;
-            }
+            res_mass<NR>(g, z, ml, mr, bv);
         }
         if (order > 0) {
             // residual of the plain start x0 = x: it judges the extrapolation
@@ -710,6 +779,252 @@ __device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, cons
     return true;
 }
 
+// ---- coarse-mesh lanes ---------------------------------------------------------
+// The lanes of pt_cm_lane.hip with the solver of this file on the coarse mesh: the
+// operator's registers are formed from the coarse element values, everything around
+// the solves reads and writes the same rows. Bound by the rounds' latency as the
+// others; 256^2, 32 slices, coarse steps on 129 x 129 nodes: 100 Jacobi rounds of
+// 10.0 us per step -> 26 of 9 (degree 3), one warm cycle 68.5 -> 23.1 ms.
+
+// The set-up of a coarse-mesh lane: as res_setup, with the step's input u restricted
+// from fine states and the norm taken of the prolonged solution. A correction sweep's
+// step needs F_n only for the next input u = x + R F_n - G(R u^k_n).
+__device__ __forceinline__ int cm_step_slice(const Consts &C, const LaunchInfo &I, int kind,
+                                             int slice, int s) {
+    const bool adj = kind == CM_GK_ADJ || kind == CM_SWEEP_ADJ;
+    if (kind == CM_GK_PRI || kind == CM_GK_ADJ) return slice;
+    if (I.cold) return adj ? C.Ntau - s : s;
+    return adj ? C.Ntau - 1 - s : s + 1;
+}
+
+template <int NR>
+__device__ __forceinline__ bool res_setup_cm(const ResGeo &g, ResLaneCtx &x,
+                                             const ResCoef<NR> &A, const double (&cc)[NR]) {
+    extern __shared__ double lds[];
+    auto is = [](unsigned m, int k) { return ResGeo::is(m, k); };
+    const EngineDesc *Dp = x.D;
+    const Consts C = fetch(&Dp->C);
+    const Bufs B = fetch(&Dp->B);
+    const LaunchInfo I = fetch(&Dp->I);
+    const CoarseMesh M = fetch(&Dp->cm);
+    const int kind = x.kind, step = x.step;
+    const bool adj = kind == CM_GK_ADJ || kind == CM_SWEEP_ADJ;
+    const bool gk = kind == CM_GK_PRI || kind == CM_GK_ADJ;
+    const bool cold = !gk && I.cold, sweep = !gk && !cold;
+    const bool prev = step > 0, next = step < x.nsteps;
+    const int np = prev ? cm_step_slice(C, I, kind, x.slice, step - 1) : 0;
+    const int n = cm_step_slice(C, I, kind, x.slice, next ? step : step - 1);
+    const double *xp = res_x(x.gv0, x.gvs, step);
+    const size_t Nn = C.Nn, Nc = M.Nc;
+    const int sz = g.sz, zlen = g.zlen, cell0 = g.cell0, Wf = C.W, LX = g.slot_x<NR>();
+    double sum[7] = {0, 0, 0, 0, 0, 0, 0};
+
+    auto waitf = [&](int fk, int k) {
+        return wait_flag(B.flags, flag_index(fk, k), I.epoch, B.ctl, C.timeout_ticks);
+    };
+    if (sweep) {
+        if (!waitf(FL_F, prev ? np : adj ? C.Ntau : 0)) return false;
+        if (!prev && !adj) x.theta = ldc(B.F_th);
+        if (next && I.gk_lanes && !waitf(FL_GK, n)) return false;
+    }
+    // the fine state of an input, the guess u^k_n and the batched output of a slice
+    auto state = [&](int k) {
+        return adj ? B.FL + (size_t)k * Nn : B.S + (size_t)(C.M * (k + 1) - 1) * Nn;
+    };
+    auto guess = [&](int k) { return (adj ? B.in_L : B.in_T) + (size_t)k * Nn; };
+    auto row = [&](int k) { return M.Gk + (size_t)k * Nc; };
+    double zc[NR], t[NR], v[NR], u[NR], bv[NR], vr[kRim], ur[kRim];
+    if (prev) {
+        g.load<NR>(xp, g.fill & ~g.own, v);
+        g.load_rim(xp, vr);
+        g.load<NR>(res_b(x.gv0, x.gvs, step), g.own & g.live, bv);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            v[k] = is(g.own, k) ? lds[LX + k * kThreads] : v[k];
+            bv[k] = is(g.own & g.live, k) ? bv[k] : 0.0;
+        }
+        g.put<NR>(0, v, vr);
+    } else {
+#pragma unroll
+        for (int k = 0; k < NR; ++k) v[k] = 0.0;
+#pragma unroll
+        for (int i = 0; i < kRim; ++i) vr[i] = 0.0;
+    }
+    // u in window 1
+    if (cold) {
+#pragma unroll
+        for (int k = 0; k < NR; ++k) u[k] = v[k];
+#pragma unroll
+        for (int i = 0; i < kRim; ++i) ur[i] = vr[i];
+    } else {
+        const double *in = sweep ? state(prev ? np : adj ? C.Ntau : 0) : guess(n);
+        g.load_fine<NR>(in, Wf, g.fill, u);
+        g.load_rim_fine(in, Wf, ur);
+        if (sweep && prev) {
+            double a[NR], ar[kRim];
+            g.load<NR>(row(np), g.fill, a);
+            g.load_rim(row(np), ar);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) u[k] = v[k] + (u[k] - a[k]);
+#pragma unroll
+            for (int i = 0; i < kRim; ++i) ur[i] = vr[i] + (ur[i] - ar[i]);
+        }
+    }
+    if (next) g.put<NR>(zlen, u, ur);
+    lds_sync();
+    if (prev) {
+        res_apply<NR>(A, cell0, sz, bv, zc, t);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const double rv = is(g.live & g.own, k) ? t[k] - cc[k] * zc[k] : 0.0;
+            sum[0] += rv * rv;
+        }
+        if (!adj) {
+            // the fine nodes of an owned node and of the edges and the cell right
+            // and above it
+            unsigned char mk[NR][4];
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int fx = 2 * g.gx + (q & 1), fy = 2 * (g.gy0 + k) + (q >> 1);
+                    const bool in = is(g.own, k) && fx <= C.nx && fy <= C.ny;
+                    const unsigned char m = *ndb(B.mask, in ? (unsigned)(fy * Wf + fx) : 0u);
+                    mk[k][q] = in ? m : 1;
+                }
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                const int z = cell0 + (k + 1) * sz;
+                const double a = lds[z], b = lds[z + 1], c = lds[z + sz], d = lds[z + sz + 1];
+                const double pv[4] = {a, 0.5 * a + 0.5 * b, 0.5 * a + 0.5 * c,
+                                      0.25 * a + 0.25 * b + 0.25 * c + 0.25 * d};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sum[1] += mk[k][q] ? 0.0 : ipow(pv[q], C.p);
+            }
+        }
+    }
+    if (next) {
+        // ---- b, x0, r0 -------------------------------------------------------------
+        if (!adj) {
+            const double qn = B.qt[C.M * (n + 1)];
+            g.load<NR>(M.fc, g.live, bv);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) bv[k] *= qn;
+        } else {
+            // P^T of the fine source: weights 1, 1/2, 1/4 of the fine nodes around
+            const double *Tm = B.S + (size_t)(C.M * (n - 1)) * Nn;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                double tv[9];
+                unsigned char mk[9];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    const int fx = 2 * g.gx + q % 3 - 1, fy = 2 * (g.gy0 + k) + q / 3 - 1;
+                    const bool in = is(g.live, k) && fx >= 0 && fx <= C.nx && fy >= 0 &&
+                                    fy <= C.ny;
+                    const unsigned id = in ? (unsigned)(fy * Wf + fx) : 0u;
+                    tv[q] = ldg(Tm, id);
+                    const unsigned char m = *ndb(B.mask, id);
+                    mk[q] = in ? m : 1;
+                }
+                double sv = 0.0;
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    const double w = (q % 3 == 1 ? 1.0 : 0.5) * (q / 3 == 1 ? 1.0 : 0.5);
+                    sv += mk[q] ? 0.0 : w * (x.src_scale * ipow(tv[q], C.p - 1));
+                }
+                bv[k] = sv;
+            }
+        }
+        {
+            double ml[NR + 1], mr[NR + 1];
+            g.cm_mass<NR>(C, M, ml, mr);
+            res_mass<NR>(g, zlen + cell0, ml, mr, bv);
+        }
+        // x0: the input, in a correction sweep G(R u^k_n) + (u - R u^k_n)
+        if (sweep) {
+            double a[NR], ar[kRim];
+            g.load<NR>(row(n), g.fill, v);
+            g.load_rim(row(n), vr);
+            g.load_fine<NR>(guess(n), Wf, g.fill, a);
+            g.load_rim_fine(guess(n), Wf, ar);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) v[k] += u[k] - a[k];
+#pragma unroll
+            for (int i = 0; i < kRim; ++i) vr[i] += ur[i] - ar[i];
+        } else {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) v[k] = u[k];
+#pragma unroll
+            for (int i = 0; i < kRim; ++i) vr[i] = ur[i];
+        }
+        lds_sync();
+        g.put<NR>(0, v, vr);
+        lds_sync();
+        res_apply<NR>(A, cell0, sz, bv, zc, t);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            t[k] = is(g.live, k) ? t[k] - cc[k] * zc[k] : 0.0;
+            const double bo = is(g.own, k) ? bv[k] : 0.0, ro = is(g.own, k) ? t[k] : 0.0;
+            sum[2] += bo * bo;
+            sum[3] += ro * ro;
+        }
+    }
+    if (prev) {
+#pragma unroll
+        for (int k = 0; k < NR; ++k) v[k] = lds[LX + k * kThreads];
+        double *out = (sweep ? M.Gn : M.Gk) + (size_t)np * Nc;
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            if (is(g.own, k)) {
+                stg(xp, g.id(k), v[k]);
+                stg(out, g.id(k), v[k]);
+            }
+    }
+    if (next) {
+        g.store<NR>(res_b(x.gv0, x.gvs, step + 1), g.own, bv);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) lds[LX + k * kThreads] = zc[k];
+        lds_sync();
+        if (g.act) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) lds[zlen + cell0 + (k + 1) * sz] = t[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 7; ++k) x.sum[k] = sum[k];
+    return true;
+}
+
+// theta, outputs and flags of a finished coarse-mesh solve (Alg. 1 with dtau and N_tau)
+__device__ __forceinline__ void res_commit_cm(ResLaneCtx &x, double pn, double relres) {
+    const EngineDesc *Dp = x.D;
+    const Consts C = fetch(&Dp->C);
+    const Bufs B = fetch(&Dp->B);
+    const LaunchInfo I = fetch(&Dp->I);
+    const int kind = x.kind, n = cm_step_slice(C, I, kind, x.slice, x.step - 1);
+    const bool gk = kind == CM_GK_PRI || kind == CM_GK_ADJ;
+    if (kind == CM_GK_PRI || kind == CM_SWEEP_PRI) {
+        const double thG = pow_call(ipow(x.theta, C.p) + pn * C.inv_NtauNe, C.inv_p);
+        x.theta = thG;
+        if (gk || I.cold) {
+            if (x.leader) B.Gk_th[n] = thG;
+        } else {
+            x.theta = thG + ldc(B.F_th + n) - ldc(B.Gk_th + n);
+            if (x.leader) {
+                B.Gn_th[n] = thG;
+                B.out_th[n + 1] = x.theta;
+            }
+        }
+    }
+    if (x.leader) {
+        if (!isfinite(relres)) set_status(B.ctl, -5);
+        if (gk) set_flag(B.flags, flag_index(FL_GK, n), I.epoch);
+        if (x.step - 1 < x.trace_steps)
+            x.trec[TR_HDR + x.step - 1] = (unsigned long long)now_ticks();
+    }
+}
+
 // The true residual of the finished solve again, x taken back from the history:
 // left at the owned nodes' cells of window 1.
 template <int NR>
@@ -807,7 +1122,8 @@ __device__ __forceinline__ void res_commit(const ResGeo &geo, ResLaneCtx &x, dou
 // Runs lane L of design *Dp on this workgroup's group (rank of g workgroups);
 // returns false when a wait timed out or another workgroup aborted, alike in
 // every workgroup.
-template <int NR, bool TIMED, bool SPLIT>
+// CM: L is a coarse-mesh lane, the grid the coarse mesh's.
+template <int NR, bool TIMED, bool SPLIT, bool CM = false>
 __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, const Launch &S,
                                          const Group &G, unsigned *bar, double *part,
                                          unsigned &nbar, unsigned long long *trec, double *red) {
@@ -817,7 +1133,8 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
     const int rank = blockIdx.x - G.wg0, g = G.nwg;
     const int tid = threadIdx.x;
     const bool leader = rank == 0 && tid == 0;
-    const bool is_adj = is_adjoint_kind(L.kind);
+    const bool is_adj =
+        CM ? L.kind == CM_GK_ADJ || L.kind == CM_SWEEP_ADJ : is_adjoint_kind(L.kind);
     const bool fine = L.kind == F_PRI || L.kind == F_ADJ;
     ResGeo q;
     ResLaneCtx x;
@@ -835,9 +1152,9 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         tmo = C.timeout_ticks;
         rtol = C.rtol;
         max_iter = C.max_iter;
-        coarse_iters = fine ? 0 : C.coarse_iters;
-        verify = C.verify || C.fp32;
-        max_restarts = C.fp32 ? C.max_restarts : 2;
+        coarse_iters = fine || CM ? 0 : C.coarse_iters;
+        verify = CM || C.verify || C.fp32;
+        max_restarts = CM ? 3 : C.fp32 ? C.max_restarts : 2;
         x.D = Dp;
         x.gv0 = group_vec(B, G.vec, V_R0);
         x.gvs = B.pool_stride;
@@ -848,7 +1165,11 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         x.trunc = coarse_iters > 0;
         x.leader = leader;
         x.step = 0;
-        x.nsteps = lane_steps(C, L.kind);
+        if constexpr (CM)
+            x.nsteps = L.kind == CM_GK_PRI || L.kind == CM_GK_ADJ ? 1
+                                                                   : C.Ntau - (I.cold ? 0 : 1);
+        else
+            x.nsteps = lane_steps(C, L.kind);
         x.sp_n = x.sp_j = x.sp_jprev = x.st_n = x.st_j = x.st_jprev = 0;
         x.order = 0;
         x.ext_cap = 1;
@@ -861,11 +1182,20 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         }
         if (L.kind == F_PRI) {
             if (L.slice > 0 && !I.cold && !C.plt) x.theta = ipow(B.in_th[L.slice], C.p);
-        } else if (L.kind == GK_PRI) {
+        } else if (L.kind == GK_PRI || L.kind == CM_GK_PRI) {
             x.theta = B.in_th[L.slice];
         }
         // geometry: owned rectangle, window, this thread's column and rows
-        const int W = C.W, HN = C.ny + 1;
+        int W = C.W, HN = C.ny + 1;
+        if constexpr (CM) {
+            const CoarseMesh M = fetch(&Dp->cm);
+            W = M.Wc;
+            HN = M.nyc + 1;
+        }
+        // a coarse node is fixed iff its fine node is
+        auto fixed = [&](int y, int gx) {
+            return B.mask[CM ? (size_t)(2 * y) * C.W + 2 * gx : (size_t)y * W + gx] != 0;
+        };
         const int deg = coarse_iters > 0 ? 0 : L.deg;
         const int TX = (W + L.tw - 1) / L.tw, TY = (HN + L.th - 1) / L.th;
         const int hx = TX > 1 ? deg + 1 : 0, hy = TY > 1 ? deg + 1 : 0;
@@ -890,7 +1220,7 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         for (int k = 0; k < NR; ++k) {
             const int y = q.gy0 + k, row = row0 + k;
             if (!inx || y < 0 || y >= HN || row > wr) continue;
-            const bool free_ = B.mask[(size_t)y * W + q.gx] == 0;
+            const bool free_ = !fixed(y, q.gx);
             if (free_) q.fill |= 1u << k;
             if (row >= wr) continue;
             if (free_) q.live |= 1u << k;
@@ -918,11 +1248,12 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
             const int gx = ox0 - hx - 1 + cx, gy = oy0 - hy - 1 + cy;
             const bool in = e < 2 * q.sz + 2 * rows && gx >= 0 && gx < W && gy >= 0 && gy < HN &&
                             cy <= wr + 1 && ty < TY;
-            const int id = in ? gy * W + gx : -1;
-            q.rim_id[i] = in && B.mask[id] == 0 ? id : -1;
+            q.rim_id[i] = in && !fixed(gy, gx) ? gy * W + gx : -1;
             q.rim_cell[i] = cy * q.sz + cx;
         }
-        const double ms = fine ? C.inv_dt : C.inv_dtau;
+        // (a coarse element's quotient k/m lies between a quarter of the least and of
+        // the largest fine one: its k and c are means, its area four times theirs)
+        const double ms = (fine ? C.inv_dt : C.inv_dtau) * (CM ? 4.0 : 1.0);
         double lo, hi;
         res_bounds(C, __longlong_as_double((long long)ctl->kmin_bits) / ms,
                    __longlong_as_double((long long)ctl->kmax_bits) / ms, lo, hi);
@@ -1075,8 +1406,14 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
     {
         const Consts C = fetch(&Dp->C);
         const Bufs B = fetch(&Dp->B);
-        q.coefs<NR>(C, B, fine, A, cc);
         const double *dg = fine ? B.dinv_f : B.dinv_c;
+        if constexpr (CM) {
+            const CoarseMesh M = fetch(&Dp->cm);
+            q.cm_coefs<NR>(C, M, A, cc);
+            dg = M.dinv;
+        } else {
+            q.coefs<NR>(C, B, fine, A, cc);
+        }
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             const double d = *nd(dg, is(live, k) ? id_of(k) : 0u);
@@ -1093,7 +1430,11 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         double sum[3] = {0.0, 0.0, 0.0};  // (r, u), (u, w), (r, r)
         x.step = step;
         if (!restart) {
-            if (!res_setup<NR>(q, x, A, cc)) return false;
+            if constexpr (CM) {
+                if (!res_setup_cm<NR>(q, x, A, cc)) return false;
+            } else {
+                if (!res_setup<NR>(q, x, A, cc)) return false;
+            }
         } else {
             res_residual<NR>(q, x, A, cc);
 #pragma unroll
@@ -1148,11 +1489,13 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
                 }
             }
             if (prev) {
-                res_commit<NR>(q, x, tot[1]);
+                if constexpr (CM) res_commit_cm(x, tot[1], relres);
+                else res_commit<NR>(q, x, tot[1]);
                 iters_all += iter;
                 iters_max = max(iters_max, iter);
                 relres_max = max(relres_max, __double_as_longlong(relres));
-            } else if (leader && L.kind == SWEEP_PRI) {
+            } else if (leader && (CM ? L.kind == CM_SWEEP_PRI && !fetch(&Dp->I).cold
+                                     : L.kind == SWEEP_PRI)) {
                 fetch(&Dp->B).out_th[1] = x.theta;
             }
             if (last) break;
@@ -1300,18 +1643,19 @@ __global__ void __launch_bounds__(kThreads) k_resident(const EngineDesc *__restr
         }
         const Lane L = S.lanes[lane_id];
         unsigned long long *trec = S.trace + (size_t)lane_id * S.trace_stride;
+        const EngineDesc *E = D + (MULTI ? L.design : 0);
+        ctl = E->B.ctl;
         if constexpr (CMESH) {
             if (is_cm_kind(L.kind)) {
-                ctl = E1.B.ctl;
-                const long long r = cm_lane(D, L.kind, L.slice, rank, G.nwg, G.vec, bar, part,
-                                            nbar, trec, S.trace_stride - TR_HDR);
-                ok = r >= 0;
-                nbar = (unsigned)r;
+                if (L.nr <= 2)
+                    ok = res_lane<2, false, false, true>(E, L, S, G, bar, part, nbar, trec, red);
+                else if (L.nr <= 4)
+                    ok = res_lane<4, false, false, true>(E, L, S, G, bar, part, nbar, trec, red);
+                else
+                    ok = res_lane<6, false, false, true>(E, L, S, G, bar, part, nbar, trec, red);
                 continue;
             }
         }
-        const EngineDesc *E = D + (MULTI ? L.design : 0);
-        ctl = E->B.ctl;
         if (L.nr <= 2)
             ok = res_lane<2, TIMED, !CMESH>(E, L, S, G, bar, part, nbar, trec, red);
         else if (L.nr <= 4)

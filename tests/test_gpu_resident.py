@@ -88,3 +88,22 @@ def test_grids_that_leave_one_group_beside_the_sweep(gpu, nx, ny, propagator, wa
     if propagator == 0:
         assert len(set(wgs.values())) == 1
     assert max(e.values()) <= 1e-10
+
+
+@pytest.mark.parametrize("nx,ny", [(2, 60), (44, 2), (90, 74), (126, 130)])
+@pytest.mark.parametrize("tuning", [dict(resident_npt_max=2), dict(resident_npt_max=4),
+                                    dict(cm_sweep_wgs=1), dict(resident=0)])
+def test_coarse_mesh_lanes(gpu, nx, ny, tuning):
+    """Coarse-mesh lanes on every number of window rows, on one workgroup, and in a
+    streaming launch; cold and warm (condition numbers as above)."""
+    cfg = _cfg(nx=nx, ny=ny, n_steps=16, n_slices=4, propagator=2, cmin=0.5, pc=2.0,
+               tuning=tuning)
+    rho = density_uniform_noise(nx, ny, nx + 3 * ny)
+    _check(cfg, rho)
+    o = run_oracle(cfg, rho)
+    rho = np.clip(rho + 0.02, 0.0, 1.0)
+    g = run_gpu(cfg, rho, (o["uT"], o["utheta"], o["lam"]), with_status=True)
+    e = compare(g, run_oracle(cfg, rho, (o["uT"], o["utheta"], o["lam"])))
+    print("warm", e, g["status"], flush=True)
+    assert g["status"]["status"] == 0
+    assert max(e.values()) <= 1e-10
