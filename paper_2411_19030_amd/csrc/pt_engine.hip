@@ -986,54 +986,67 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                        a[4] * LV[li - W] + a[5] * LV[li + W + 1] + a[6] * LV[li + W - 1] +
                        a[7] * LV[li - W + 1] + a[8] * LV[li - W - 1];
             };
-            auto dinv_row = [&](int l, int id, const Real(&a)[9]) -> Real {
-                if (l == 0) return (Real)dinv0[id];
-                return a[0] != (Real)0 ? (Real)1 / a[0] : (Real)0;
-            };
             // Nodes [a, b) of level l in LDS-sized chunks. The chunk's operand
             // window (one grid row and one node of halo on each side) is staged
             // with coalesced device-coherent loads: value(id) = v[id], plus the
             // bilinear prolongation of e when e is given (0 on Dirichlet nodes
-            // of level 0). Then, kU nodes per thread at a time, ld(id) issues a
+            // of level 0). Then, kG nodes per thread at a time, ld(id) issues a
             // node's loads and op(id, li, W, vals) computes and stores.
+            //
+            // A pass is bound by the latency of its loads (512^2 nodes on 8
+            // workgroups: 64 nodes a thread, 0.35 TB/s from memory, vector units
+            // 10% busy), so no load stands in a branch of its own, where its use
+            // would wait for it: nodes outside read a node inside, and all loads
+            // of kG nodes are in flight together. 39 -> 29 us per pass of 22
+            // such groups (6 nodes: with 8 the kernel spills).
+            constexpr int kG = sizeof(Real) == 4 ? 6 : 4;
             auto staged = [&](int l, const Real *v, const Real *e, int a, int b, auto &&ld,
                               auto &&opf) {
+                constexpr int N = kG;
                 const Lvl Lv = gmg_level(C, l);
                 const int Hl = Lv.W + 1;
                 for (int c0 = a; c0 < b; c0 += C.gmg_chunk) {
                     const int c1 = min(c0 + C.gmg_chunk, b);
                     const int lo = c0 - Hl, len = (c1 - c0) + 2 * Hl;
                     lds_sync();
-                    for (int q0 = threadIdx.x; q0 < len; q0 += kThreads * kU) {
-                        Real vv[kU];
+                    for (int q0 = threadIdx.x; q0 < len; q0 += kThreads * N) {
+                        Real vv[N];
+                        bool in[N];
 #pragma unroll
-                        for (int u = 0; u < kU; ++u) {
-                            const int q = q0 + u * kThreads;
-                            const int id = lo + q;
-                            Real x = 0;
-                            if (q < len && id >= 0 && id < Lv.Nn) {
-                                x = ldc(v + id);
-                                if (e) x += gmg_prolong<Real>(C, l, id, e);
-                                if (l == 0 && B.mask[id]) x = 0;
-                            }
-                            vv[u] = x;
+                        for (int u = 0; u < N; ++u) {
+                            const int q = q0 + u * kThreads, id = lo + q;
+                            in[u] = q < len && id >= 0 && id < Lv.Nn;
+                            vv[u] = ldc(v + (in[u] ? id : 0));
+                        }
+                        if (l == 0) {
+                            unsigned char mk[N];
+#pragma unroll
+                            for (int u = 0; u < N; ++u)
+                                mk[u] = B.mask[in[u] ? lo + q0 + u * kThreads : 0];
+#pragma unroll
+                            for (int u = 0; u < N; ++u) in[u] = in[u] && mk[u] == 0;
+                        }
+                        if (e) {
+                            Prolong<Real> pr[N];
+#pragma unroll
+                            for (int u = 0; u < N; ++u)
+                                pr[u].load(C, l, in[u] ? lo + q0 + u * kThreads : 0, e);
+#pragma unroll
+                            for (int u = 0; u < N; ++u) vv[u] += pr[u].value();
                         }
 #pragma unroll
-                        for (int u = 0; u < kU; ++u) {
+                        for (int u = 0; u < N; ++u) {
                             const int q = q0 + u * kThreads;
-                            if (q < len) LV[q] = vv[u];
+                            if (q < len) LV[q] = in[u] ? vv[u] : (Real)0;
                         }
                     }
                     lds_sync();
-                    for (int id0 = c0 + threadIdx.x; id0 < c1; id0 += kThreads * kU) {
-                        decltype(ld(0)) vals[kU];
+                    for (int id0 = c0 + threadIdx.x; id0 < c1; id0 += kThreads * N) {
+                        decltype(ld(0)) vals[N];
 #pragma unroll
-                        for (int u = 0; u < kU; ++u) {
-                            const int id = id0 + u * kThreads;
-                            if (id < c1) vals[u] = ld(id);
-                        }
+                        for (int u = 0; u < N; ++u) vals[u] = ld(min(id0 + u * kThreads, c1 - 1));
 #pragma unroll
-                        for (int u = 0; u < kU; ++u) {
+                        for (int u = 0; u < N; ++u) {
                             const int id = id0 + u * kThreads;
                             if (id < c1) opf(id, id - lo, Lv.W, vals[u]);
                         }
@@ -1046,14 +1059,19 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 a = min(rank * ts, Nl);
                 b = min(a + ts, Nl);
             };
-            auto own = [&](int l, auto &&f) {
-                int a, b;
-                own_range(l, a, b);
-                for (int id = a + threadIdx.x; id < b; id += kThreads) f(id);
-            };
-            auto whole = [&](int l, auto &&f) {
-                const int Nl = gmg_level(C, l).Nn;
-                for (int id = threadIdx.x; id < Nl; id += kThreads) f(id);
+            // ld(id), then op(id, vals) at nodes [a, b), N nodes per thread at a time
+            auto nodes = [&](auto n_, int a, int b, auto &&ld, auto &&opf) {
+                constexpr int N = decltype(n_)::value;
+                for (int id0 = a + threadIdx.x; id0 < b; id0 += kThreads * N) {
+                    decltype(ld(0)) vals[N];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) vals[u] = ld(min(id0 + u * kThreads, b - 1));
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        const int id = id0 + u * kThreads;
+                        if (id < b) opf(id, vals[u]);
+                    }
+                }
             };
             // between passes of the single-workgroup levels: every wave's
             // device-coherent stores must have landed before another wave of
@@ -1066,7 +1084,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
             };
             struct RowR {
                 Real a[9];
-                Real r;
+                Real r, d;
             };
             // lb_l = r_l - A_l la_l on nodes [a, b)
             auto resid_pass = [&](int l, int a, int b) {
@@ -1088,37 +1106,76 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                            RowR x;
                            row(l, id, x.a);
                            x.r = ldc(lr(l) + id);
+                           x.d = (Real)0;
+                           if (l == 0) x.d = (Real)dinv0[id];
                            return x;
                        },
                        [&](int id, int li, int W, const RowR &x) {
-                           stc(dst + id, LV[li] + omega(l) * dinv_row(l, id, x.a) *
-                                                      (x.r - apply_lds(x.a, li, W)));
+                           const Real d = l == 0               ? x.d
+                                          : x.a[0] != (Real)0 ? (Real)1 / x.a[0]
+                                                              : (Real)0;
+                           stc(dst + id, LV[li] + omega(l) * d * (x.r - apply_lds(x.a, li, W)));
                        });
             };
-            auto restr = [&](int l, int I) {  // r_{l+1} = P^T lb_l, la_{l+1} = omega D^{-1} r_{l+1}
-                const Real rc = gmg_restrict<Real>(C, l, I, lb(l));
-                stc(lr(l + 1) + I, rc);
-                const Real c = reinterpret_cast<const Real *>(B.gA)[(size_t)op * 9 * gn +
-                                                                     C.gmg_off[l + 1] + I];
-                stc(la(l + 1) + I, c != (Real)0 ? omega(l + 1) * rc / c : (Real)0);
+            // r_{l+1} = P^T lb_l, la_{l+1} = omega D^{-1} r_{l+1} on nodes [a, b) of l + 1
+            auto restr_pass = [&](int l, int a, int b) {
+                struct RestrC {
+                    Restrict<Real> r;
+                    Real c;
+                };
+                const Real om = omega(l + 1);
+                auto ld = [&](int I) {
+                    RestrC x;
+                    x.r.load(C, l, I, lb(l));
+                    x.c = reinterpret_cast<const Real *>(
+                        B.gA)[(size_t)op * 9 * gn + C.gmg_off[l + 1] + I];
+                    return x;
+                };
+                auto put = [&](int I, const RestrC &x) {
+                    const Real rc = x.r.value();
+                    stc(lr(l + 1) + I, rc);
+                    stc(la(l + 1) + I, x.c != (Real)0 ? om * rc / x.c : (Real)0);
+                };
+                nodes(std::integral_constant<int, kG / 2>{}, a, b, ld, put);
             };
 
             // pointwise CG update (u of the previous round is in UB0) and the
             // first smoothing step u1 = omega D^{-1} r
-            own(0, [&](int id) {
-                Real r = ldc(R + id);
+            {
+                int a, b;
+                own_range(0, a, b);
+                const Real om0 = omega(0);
                 if (update) {
-                    const Real w = ldc(Wv + id), u = ldc(UB0 + id);
-                    const Real sn = first ? w : w + (Real)be * ldc(Sv + id);
-                    const Real pn = first ? u : u + (Real)be * ldc(P + id);
-                    stc(Sv + id, sn);
-                    stc(P + id, pn);
-                    stc(X + id, ldc(X + id) + al * (double)pn);
-                    r = r - (Real)al * sn;
-                    stc(R + id, r);
+                    struct Upd {
+                        Real r, w, u, s, p;
+                        double x, d;
+                    };
+                    nodes(std::integral_constant<int, kG>{}, a, b,
+                          [&](int id) {
+                              // (s and p of the first round are read and not used)
+                              return Upd{ldc(R + id),  ldc(Wv + id), ldc(UB0 + id), ldc(Sv + id),
+                                         ldc(P + id), ldc(X + id),  dinv0[id]};
+                          },
+                          [&](int id, const Upd &v) {
+                              const Real sn = first ? v.w : v.w + (Real)be * v.s;
+                              const Real pn = first ? v.u : v.u + (Real)be * v.p;
+                              stc(Sv + id, sn);
+                              stc(P + id, pn);
+                              stc(X + id, v.x + al * (double)pn);
+                              const Real r = v.r - (Real)al * sn;
+                              stc(R + id, r);
+                              stc(U + id, om0 * (Real)v.d * r);
+                          });
+                } else {
+                    struct Start {
+                        Real r;
+                        double d;
+                    };
+                    nodes(std::integral_constant<int, kG>{}, a, b,
+                          [&](int id) { return Start{ldc(R + id), dinv0[id]}; },
+                          [&](int id, const Start &v) { stc(U + id, om0 * (Real)v.d * v.r); });
                 }
-                stc(U + id, omega(0) * (Real)dinv0[id] * r);
-            });
+            }
             const int Lv = C.gmg_L, Lg = C.gmg_Lg;
             for (int l = 0; l < Lg; ++l) {
                 if (!barrier(false)) return false;
@@ -1129,7 +1186,9 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 }
                 if (l + 1 < Lv) {
                     if (!barrier(false)) return false;
-                    own(l + 1, [&](int I) { restr(l, I); });
+                    int a, b;
+                    own_range(l + 1, a, b);
+                    restr_pass(l, a, b);
                 }
             }
             if (Lg < Lv) {
@@ -1138,7 +1197,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                     for (int l = Lg; l < Lv - 1; ++l) {
                         resid_pass(l, 0, gmg_level(C, l).Nn);
                         wg_sync();
-                        whole(l + 1, [&](int I) { restr(l, I); });
+                        restr_pass(l, 0, gmg_level(C, l + 1).Nn);
                         wg_sync();
                     }
                     // coarsest level: an odd number of damped Jacobi sweeps, the
@@ -1301,21 +1360,36 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                         const int lo = c0 - H, len = (c1 - c0) + 2 * H;
                         lds_sync();
                         for (int q0 = threadIdx.x; q0 < len; q0 += kThreads * kU) {
+                            // (no load in a branch of its own, as in the rounds)
                             double vt[kU], vx[kU];
+                            unsigned char mk[kU];
+                            auto at_ = [&](int u) {
+                                const int id = lo + q0 + u * kThreads;
+                                return id >= 0 && id < C.Nn ? id : 0;
+                            };
 #pragma unroll
                             for (int u = 0; u < kU; ++u) {
-                                const int q = q0 + u * kThreads;
-                                vt[u] = q < len ? ldm(ts, lo + q) : 0.0;
-                                vx[u] = q < len ? ldm(xs, lo + q) : 0.0;
-                                if (q < len && first_entry && st.d1)
-                                    vx[u] += ldm(st.d1, lo + q) - ldm(st.d0, lo + q);
+                                vt[u] = ldc(ts + at_(u));
+                                vx[u] = ldc(xs + at_(u));
+                                mk[u] = B.mask[at_(u)];
+                            }
+                            if (first_entry && st.d1) {
+                                double v1[kU], v0[kU];
+#pragma unroll
+                                for (int u = 0; u < kU; ++u) {
+                                    v1[u] = ldc(st.d1 + at_(u));
+                                    v0[u] = ldc(st.d0 + at_(u));
+                                }
+#pragma unroll
+                                for (int u = 0; u < kU; ++u) vx[u] += v1[u] - v0[u];
                             }
 #pragma unroll
                             for (int u = 0; u < kU; ++u) {
-                                const int q = q0 + u * kThreads;
+                                const int q = q0 + u * kThreads, id = lo + q;
                                 if (q < len) {
-                                    WT[q] = vt[u];
-                                    WX[q] = vx[u];
+                                    const bool in = id >= 0 && id < C.Nn && mk[u] == 0;
+                                    WT[q] = in ? vt[u] : 0.0;
+                                    WX[q] = in ? vx[u] : 0.0;
                                 }
                             }
                         }

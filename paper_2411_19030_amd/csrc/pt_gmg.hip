@@ -121,43 +121,58 @@ __device__ __forceinline__ Real gmg_apply(const Consts &C, const Bufs &B, int op
     return s;
 }
 
-// Restriction P^T of level-l values to coarse node I of level l+1.
+// One node of the restriction P^T v (the nine fine nodes around coarse node I), and of
+// the prolongation P e: loads first, all unconditional (terms outside the grid
+// or not needed read a node inside), then the value.
 template <typename Real>
-__device__ __forceinline__ Real gmg_restrict(const Consts &C, int l, int I, const Real *v) {
-    const Lvl F = gmg_level(C, l);
-    const Lvl G = gmg_level(C, l + 1);
-    const int Iy = I / G.W, Ix = I - Iy * G.W;
-    Real s = 0;
+struct Restrict {
+    Real v[9];
+    bool in[9];
+    __device__ __forceinline__ void load(const Consts &C, int l, int I, const Real *f) {
+        const Lvl F = gmg_level(C, l);
+        const Lvl G = gmg_level(C, l + 1);
+        const int Iy = I / G.W, Ix = I - Iy * G.W;
 #pragma unroll
-    for (int b = -1; b <= 1; ++b) {
-        const int fy = 2 * Iy + b;
-        if (fy < 0 || fy > F.ny) continue;
-        const Real wy = b == 0 ? (Real)1 : (Real)0.5;
-#pragma unroll
-        for (int a = -1; a <= 1; ++a) {
-            const int fx = 2 * Ix + a;
-            if (fx < 0 || fx > F.nx) continue;
-            const Real wx = a == 0 ? (Real)1 : (Real)0.5;
-            s += wx * wy * ldc(v + fy * F.W + fx);
+        for (int k = 0; k < 9; ++k) {
+            const int fy = 2 * Iy + k / 3 - 1, fx = 2 * Ix + k % 3 - 1;
+            in[k] = fy >= 0 && fy <= F.ny && fx >= 0 && fx <= F.nx;
+            v[k] = ldc(f + (in[k] ? fy * F.W + fx : 0));
         }
     }
-    return s;
-}
+    __device__ __forceinline__ Real value() const {
+        Real s = 0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const Real wy = k / 3 == 1 ? (Real)1 : (Real)0.5, wx = k % 3 == 1 ? (Real)1 : (Real)0.5;
+            s += wx * wy * (in[k] ? v[k] : (Real)0);
+        }
+        return s;
+    }
+};
 
-// Bilinear prolongation of level-(l+1) values to fine node id of level l.
 template <typename Real>
-__device__ __forceinline__ Real gmg_prolong(const Consts &C, int l, int id, const Real *e) {
-    const Lvl F = gmg_level(C, l);
-    const Lvl G = gmg_level(C, l + 1);
-    const int fy = id / F.W, fx = id - fy * F.W;
-    const int x0 = fx >> 1, y0 = fy >> 1;
-    const bool ox = fx & 1, oy = fy & 1;
-    if (!ox && !oy) return ldc(e + y0 * G.W + x0);
-    if (ox && !oy) return (Real)0.5 * (ldc(e + y0 * G.W + x0) + ldc(e + y0 * G.W + x0 + 1));
-    if (!ox && oy) return (Real)0.5 * (ldc(e + y0 * G.W + x0) + ldc(e + (y0 + 1) * G.W + x0));
-    return (Real)0.25 * (ldc(e + y0 * G.W + x0) + ldc(e + y0 * G.W + x0 + 1) +
-                         ldc(e + (y0 + 1) * G.W + x0) + ldc(e + (y0 + 1) * G.W + x0 + 1));
-}
+struct Prolong {
+    Real a, b, c, d;
+    bool ox, oy;
+    __device__ __forceinline__ void load(const Consts &C, int l, int id, const Real *e) {
+        const Lvl F = gmg_level(C, l);
+        const Lvl G = gmg_level(C, l + 1);
+        const int fy = id / F.W, fx = id - fy * F.W;
+        ox = fx & 1;
+        oy = fy & 1;
+        const Real *p = e + (fy >> 1) * G.W + (fx >> 1);
+        const int dx = ox ? 1 : 0, dy = oy ? G.W : 0;
+        a = ldc(p);
+        b = ldc(p + dx);
+        c = ldc(p + dy);
+        d = ldc(p + dy + dx);
+    }
+    __device__ __forceinline__ Real value() const {
+        const Real x = (Real)0.5 * (a + b), y = (Real)0.5 * (a + c);
+        const Real xy = (Real)0.25 * (a + b + c + d);
+        return ox ? (oy ? xy : x) : (oy ? y : a);
+    }
+};
 
 }  // namespace
 
