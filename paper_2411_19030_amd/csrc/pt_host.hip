@@ -887,14 +887,38 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         if (is_cm_kind(kind)) return (C.nx / 2) * (C.ny / 2) <= 48 * 48 ? 1 : deg_f;
         return C.coarse_iters > 0 ? 0 : deg_c;
     };
-    // the lane's degree, or the largest below it whose window fits
     auto rows_of = [&](int kind) { return is_cm_kind(kind) ? C.ny / 2 + 1 : HN; };
     auto width_of = [&](int kind) { return is_cm_kind(kind) ? C.nx / 2 + 1 : C.W; };
+    // The lane's shape on at most max_wg workgroups: its degree, or the largest below
+    // it whose window fits; then, among the degrees from one less up to kResMaxDeg and
+    // the rows per thread, the least time per application of the operator. A round of
+    // n = degree + 1 applications takes about 3 + 0.5 rows + n (0.1 + 0.12 rows) us
+    // (measured: 5.4 at 2 rows and n = 4, 9.3 at 6 rows), and the polynomial's part in
+    // the convergence falls off by some 3% per degree. More applications per round pay
+    // until the window's rings need more rows (101^2 nodes, sequential: 105 ms at
+    // degree 3, 75 at 8; sweep of 30 slices 13.2 ms at 4, 11.5 at 6).
     auto fit = [&](int kind, int max_wg, Shape &s, int &n) {
-        for (int deg = deg_of(kind); deg >= 0; --deg)
-            if (res_shape(width_of(kind), rows_of(kind), max_wg, deg, rows_max, cap, s, n))
-                return true;
-        return false;
+        const int W = width_of(kind), H = rows_of(kind), d0 = deg_of(kind);
+        bool ok = false;
+        for (int deg = d0; deg >= 0 && !ok; --deg)
+            ok = res_shape(W, H, max_wg, deg, rows_max, cap, s, n);
+        if (!ok || d0 < 2 || s.deg < d0) return ok;
+        auto cost = [](int nr, int apps) {
+            return (3.0 + 0.5 * nr + apps * (0.1 + 0.12 * nr)) / apps * (1.0 + 0.03 * apps);
+        };
+        for (int deg = d0 - 1; deg <= kResMaxDeg; ++deg) {
+            Shape t;
+            int m;
+            if (!res_shape(W, H, max_wg, deg, rows_max, cap, t, m)) break;
+            // (one degree less only for the fastest rounds: at 512^2, 4 rows and degree 2
+            // instead of 6 and 3 took 314 ms against 291)
+            if (deg < d0 && t.nr > kResRowChoices[0]) continue;
+            if (cost(t.nr, deg + 1) < cost(s.nr, s.deg + 1)) {
+                s = t;
+                n = m;
+            }
+        }
+        return ok;
     };
     auto min_wgs = [&](int kind, int deg) {
         return res_min_wgs(width_of(kind), rows_of(kind), deg, rows_max, cap);
@@ -1025,15 +1049,13 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     // per-round phase times: FP64 launches without coarse-mesh lanes only
     const bool timed = T.phase_timers != 0 && !C.fp32 && !cm;
     // sweep group: 40 workgroups. A resident sweep of full solves to a tight
-    // tolerance is the longest lane of the pass: it gets about 1000 nodes per
-    // workgroup within 40..64 (a quarter of the grid; measured best at 256^2
-    // and 100^2 with rtol 1e-10, the fine lanes queued ahead of the batched
-    // coarse steps); shorter sweeps (truncated or loose solves) leave the fine
-    // lanes critical, and there more sweep workgroups only slow the fine lanes
+    // tolerance is the longest lane of the pass: it gets 64 (a quarter of the grid;
+    // 64 against 40: 28.9 -> 27.6 ms at 100^2, 34.5 -> 33.8 at 199 x 150); shorter
+    // sweeps (truncated or loose solves) leave the fine lanes critical, and there
+    // more sweep workgroups only slow the fine lanes
     const int sweep_wgs = T.sweep_wgs > 0 ? T.sweep_wgs : 40;
     const bool long_sweep = C.coarse_iters == 0 && C.rtol < 1e-9;
-    const int sweep_wgs_res =
-        T.sweep_wgs > 0 ? T.sweep_wgs : long_sweep ? std::min(64, std::max(40, C.Nn / 1000)) : 40;
+    const int sweep_wgs_res = T.sweep_wgs > 0 ? T.sweep_wgs : long_sweep ? 64 : 40;
 
     std::vector<int> ngroups(plans.size()), per_group(plans.size()), nwg(plans.size());
     std::vector<Shape> shape(plans.size()), lead_shape(plans.size());

@@ -48,7 +48,7 @@ namespace pt {
 
 namespace {
 
-constexpr int kResMaxDeg = 6;       // degree of the preconditioner's polynomial
+constexpr int kResMaxDeg = 8;        // degree of the preconditioner's polynomial
 constexpr int kResRows = 6;         // most rows of a window column per thread
 constexpr int kResSums = 8;         // sums per reduction, at most
 constexpr int kResGroup = kMaxGroup / 2;  // workgroups per resident group, at most
