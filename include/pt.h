@@ -83,7 +83,7 @@ typedef struct pt_tuning {
     int32_t wg_per_cu;         /* engine workgroups per compute unit                        (1)  */
     int32_t resident;          /* -1: resident groups (vectors in registers) where they pay;    */
                                /*  0: streaming groups only; 1: resident wherever they fit  (-1) */
-    int32_t resident_npt_max;  /* nodes per thread of a resident tile, 1..8                 (8)  */
+    int32_t resident_npt_max;  /* most window rows per thread of resident lanes, 1..8       (8)  */
     int32_t sweep_wgs;         /* workgroups of a correction-sweep group; 0: by problem size (0) */
     int32_t cm_sweep_wgs;      /* workgroups of a coarse-mesh correction-sweep group        (24) */
     int32_t fine_wgs;          /* > 0: fine lanes on groups of this many workgroups, alike  */
@@ -97,11 +97,13 @@ typedef struct pt_tuning {
     int32_t tile_max;          /* largest streaming tile in nodes, >= 256                   (4096) */
     int32_t ck_slots;          /* PT_CHECKPOINT: fine-lane groups (recompute slots), >= 1;  */
                                /* fewer if the grid cannot hold them beside the sweeps  (24) */
-    int32_t extrap;            /* 1: fine steps start from 2 T_{j-1} - T_{j-2}               (0) */
+    int32_t extrap;            /* 1: fine steps start from 2 T_{j-1} - T_{j-2}; 0: resident   (0) */
+                               /*    lanes choose an extrapolation by its residual              */
     int32_t sweep_x0;          /* 1: a sweep step starts from G(u^k_n) + (u^{k+1}_n - u^k_n),  */
                                /* 0: from u^{k+1}_n                                          (1) */
     int32_t verify;            /* 1: the true residual decides a solve's convergence       (1)  */
     double inner_rtol;         /* PT_FP32_REFINE: residual reduction of one FP32 solve     (1e-5) */
+                               /* (streaming lanes; resident lanes solve in FP64)              */
     int32_t gmg_tail;          /* PT_GMG: levels of at most this many nodes run on one     */
                                /* workgroup                                                (4096) */
     int32_t gmg_sweeps;        /* PT_GMG: smoothing pairs on the coarsest level            (16)  */
@@ -149,7 +151,9 @@ typedef struct pt_problem {
 
 typedef struct pt_stats {
     int32_t status;            /* PT_OK, PT_ENOCONV or PT_EDOMAIN: first device-side problem     */
-    int32_t max_cg_iters;      /* largest CG iteration count of any solve of the last pass       */
+    int32_t max_cg_iters;      /* largest CG iteration count of any solve of the last pass; one  */
+                               /* iteration applies the preconditioner once (resident lanes: a   */
+                               /* polynomial of the operator)                                    */
     int64_t cg_iters_fine;     /* total CG iterations of fine solves (forward + adjoint)          */
     int64_t cg_iters_coarse;   /* total CG iterations of coarse solves (cold, batched, sweep)    */
     int64_t solves_fine;

@@ -847,6 +847,37 @@ bool res_shape(int W, int HN, int max_wg, int deg, int rows_max, size_t lds_cap,
     return false;
 }
 
+// The shape of lanes of degree d0 on at most max_wg workgroups: that degree, or the
+// largest below it whose window fits; then, among the degrees from one less up to
+// kResMaxDeg and the rows per thread, the least time per application of the operator.
+// A round of n = degree + 1 applications takes about 3 + 0.5 rows + n (0.1 + 0.12 rows)
+// us (measured: 5.4 at 2 rows and n = 4, 9.3 at 6 rows), and the polynomial's part in
+// the convergence falls off by some 3% per degree. More applications per round pay
+// until the window's rings need more rows (101^2 nodes, sequential: 105 ms at degree 3,
+// 71 at 8; sweep of 30 slices 13.2 ms at 4, 11.5 at 6).
+bool res_fit(int W, int HN, int max_wg, int d0, int rows_max, size_t cap, Shape &s, int &n) {
+    bool ok = false;
+    for (int deg = d0; deg >= 0 && !ok; --deg)
+        ok = res_shape(W, HN, max_wg, deg, rows_max, cap, s, n);
+    if (!ok || d0 < 2 || s.deg < d0) return ok;
+    auto cost = [](int nr, int apps) {
+        return (3.0 + 0.5 * nr + apps * (0.1 + 0.12 * nr)) / apps * (1.0 + 0.03 * apps);
+    };
+    for (int deg = d0 - 1; deg <= kResMaxDeg; ++deg) {
+        Shape t;
+        int m;
+        if (!res_shape(W, HN, max_wg, deg, rows_max, cap, t, m)) break;
+        // (one degree less only for the fastest rounds: at 512^2, 4 rows and degree 2
+        // instead of 6 and 3 took 314 ms against 291)
+        if (deg < d0 && t.nr > kResRowChoices[0]) continue;
+        if (cost(t.nr, deg + 1) < cost(s.nr, s.deg + 1)) {
+            s = t;
+            n = m;
+        }
+    }
+    return ok;
+}
+
 // The fewest workgroups that hold the grid (0: none do).
 int res_min_wgs(int W, int HN, int deg, int rows_max, size_t lds_cap) {
     int best = 0;
@@ -889,36 +920,8 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
     };
     auto rows_of = [&](int kind) { return is_cm_kind(kind) ? C.ny / 2 + 1 : HN; };
     auto width_of = [&](int kind) { return is_cm_kind(kind) ? C.nx / 2 + 1 : C.W; };
-    // The lane's shape on at most max_wg workgroups: its degree, or the largest below
-    // it whose window fits; then, among the degrees from one less up to kResMaxDeg and
-    // the rows per thread, the least time per application of the operator. A round of
-    // n = degree + 1 applications takes about 3 + 0.5 rows + n (0.1 + 0.12 rows) us
-    // (measured: 5.4 at 2 rows and n = 4, 9.3 at 6 rows), and the polynomial's part in
-    // the convergence falls off by some 3% per degree. More applications per round pay
-    // until the window's rings need more rows (101^2 nodes, sequential: 105 ms at
-    // degree 3, 75 at 8; sweep of 30 slices 13.2 ms at 4, 11.5 at 6).
     auto fit = [&](int kind, int max_wg, Shape &s, int &n) {
-        const int W = width_of(kind), H = rows_of(kind), d0 = deg_of(kind);
-        bool ok = false;
-        for (int deg = d0; deg >= 0 && !ok; --deg)
-            ok = res_shape(W, H, max_wg, deg, rows_max, cap, s, n);
-        if (!ok || d0 < 2 || s.deg < d0) return ok;
-        auto cost = [](int nr, int apps) {
-            return (3.0 + 0.5 * nr + apps * (0.1 + 0.12 * nr)) / apps * (1.0 + 0.03 * apps);
-        };
-        for (int deg = d0 - 1; deg <= kResMaxDeg; ++deg) {
-            Shape t;
-            int m;
-            if (!res_shape(W, H, max_wg, deg, rows_max, cap, t, m)) break;
-            // (one degree less only for the fastest rounds: at 512^2, 4 rows and degree 2
-            // instead of 6 and 3 took 314 ms against 291)
-            if (deg < d0 && t.nr > kResRowChoices[0]) continue;
-            if (cost(t.nr, deg + 1) < cost(s.nr, s.deg + 1)) {
-                s = t;
-                n = m;
-            }
-        }
-        return ok;
+        return res_fit(width_of(kind), rows_of(kind), max_wg, deg_of(kind), rows_max, cap, s, n);
     };
     auto min_wgs = [&](int kind, int deg) {
         return res_min_wgs(width_of(kind), rows_of(kind), deg, rows_max, cap);
@@ -1388,7 +1391,9 @@ constexpr int kBatchDegFine = 3, kBatchDegCoarse = 4;
 bool batch_shape(const Consts &C, int wgs, int deg, int lds_cap_d, int (&out)[4]) {
     Shape s{};
     int n = 0;
-    if (!res_shape(C.W, C.ny + 1, wgs, deg, kResRows, (size_t)lds_cap_d * sizeof(double), s, n))
+    const size_t cap = (size_t)lds_cap_d * sizeof(double);
+    if (!res_shape(C.W, C.ny + 1, wgs, deg, kResRows, cap, s, n) ||
+        !res_fit(C.W, C.ny + 1, wgs, deg, kResRows, cap, s, n))
         return false;
     out[0] = s.tw;
     out[1] = s.th;
@@ -1413,7 +1418,7 @@ void batch_work(const EngineDesc &E, double &all, double &sweep) {
 // time. A round is bound by latency, not by its nodes, so a group of more workgroups
 // than a design needs is wasted on it: twelve designs of 64^2 to 256^2 with 4 to 16
 // slices need 2 to 36 each (500 ms a cycle on streaming groups of 2 and 16
-// workgroups, 60 ms here). False if a design fits no group.
+// workgroups, 54 ms here). False if a design fits no group.
 bool plan_batch(std::vector<EngineDesc> &hd, int grid, int cap_d, GroupArgs &A, size_t &lds) {
     const int n = (int)hd.size();
     const size_t cap = (size_t)cap_d * sizeof(double);

@@ -40,9 +40,9 @@
 // it, lowers the order where the states are not smooth.
 //
 // Measured at 256^2, 512 steps in 32 slices, cg_rtol 1e-12, one warm cycle,
-// against Jacobi CG on full-row tiles with one halo row: 94 -> 29.5 ms; CG
+// against Jacobi CG on full-row tiles with one halo row: 94 -> 29.4 ms; CG
 // rounds per fine step 42 -> 8 (degree 3, extrapolated), per coarse step 169 ->
-// 36 (degree 4); sequential 100^2 with 480 steps: 741 -> 120 ms.
+// 36 (degree 4); sequential 100^2 with 480 steps: 741 -> 87 ms.
 
 namespace pt {
 
