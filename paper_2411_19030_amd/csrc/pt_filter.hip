@@ -59,7 +59,7 @@ __device__ __forceinline__ double proj_deriv(double f, double beta, double eta) 
 // Windows that fit the LDS in pieces
 // ---------------------------------------------------------------------------
 
-constexpr int kTX = 64, kThr = 256;      // output columns, threads of a block
+constexpr int kTX = 64, kThr = 512;      // output columns, threads of a block
 constexpr int kWaves = kThr / 64;        // output rows: T per wave
 constexpr int kMinRows = 32;             // rows staged at once, at least
 constexpr size_t kLdsMax = 158 * 1024;
@@ -121,9 +121,10 @@ __device__ double direct_sum(const Geom &g, const double *x, int i, int j) {
 // T rows of 64 columns; the block's input and halo are in LDS (rc_max rows at a
 // time), rows of x(+di) + x(-di) are formed once for T outputs, and the weights of
 // a column distance lie in LDS too, formed once by all threads (two buffers, one
-// barrier per distance). Per input row and column distance a thread reads two
-// values and about two weights for T FMAs: with T = 16 the FMAs bound it, with 8 the
-// LDS. 1024^2 elements, r = 0.03 (2965 weights): forward and backward 13.5 -> 0.36 ms
+// barrier per distance). Bound by the LDS: per input row and column distance a
+// thread reads two values and about two weights for T FMAs. Eight waves of 8 rows
+// hide its latency better than four of 16 on the same tile (0.32 against 0.36 ms).
+// 1024^2 elements, r = 0.03 (2965 weights): forward and backward 13.5 -> 0.32 ms
 // against one thread per element with weights formed in place.
 template <int T, bool ADJ>
 __global__ void __launch_bounds__(kThr)
@@ -281,8 +282,8 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb) {
 }
 
 // Rows per wave, rows staged at once and LDS of k_filter_sum; T = 0 where the window
-// is too large. 16 rows where the blocks fill the device (T = 8 reads as much LDS
-// per row for half the outputs); 8 below, where half the blocks would idle.
+// is too large. 8 rows where the blocks fill the device (4 rows read as much LDS per
+// row for half the outputs); 4 below, where half the blocks would idle.
 struct SumPlan {
     int T, rc;
     size_t lds;
@@ -294,8 +295,8 @@ SumPlan sum_plan(const Geom &g) {
     };
     SumPlan P{0, 0, 0};
     if (rect_doubles(g) * sizeof(double) > kLdsMax) return P;
-    for (int T : {16, 8}) {
-        if (T == 16 && blocks(16) < 200) continue;
+    for (int T : {8, 4}) {
+        if (T == 8 && blocks(8) < 200) continue;
         const size_t row = sizeof(double) * (kTX + 2 * (size_t)g.Rx);
         const size_t wts = sizeof(double) * 2 * (2 * (size_t)g.Ry + 4 * T);
         if (wts + row * (kMinRows + T) > kLdsMax) continue;
@@ -310,7 +311,7 @@ SumPlan sum_plan(const Geom &g) {
 template <bool ADJ>
 int launch_sum(const Geom &g, const SumPlan &P, double beta, double eta, const double *x,
                double *fil, double *out, hipStream_t stream) {
-    auto kern = P.T == 16 ? k_filter_sum<16, ADJ> : k_filter_sum<8, ADJ>;
+    auto kern = P.T == 8 ? k_filter_sum<8, ADJ> : k_filter_sum<4, ADJ>;
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)P.lds) != hipSuccess)
         return PT_EHIP;
