@@ -59,9 +59,11 @@ def test_filter_projection_against_oracle(gpu, nx, ny, r, beta, eta):
 
 # around the edges of a block's tile (64 columns; 8 waves of 4 or 8 rows) and of
 # the pieces its rows are staged in, windows wider or higher than the grid, the
-# 8-row form (at least 200 blocks) and, at r = 0.8, a window of one thread per element
+# 8-row form (at least 200 blocks) and, at 340 columns, the form of one thread per
+# element
 EDGES = [(63, 31, 0.05), (64, 32, 0.05), (65, 33, 0.05), (1, 70, 0.2), (130, 1, 0.1),
-         (128, 64, 0.3), (200, 20, 0.9), (300, 12, 0.8), (1600, 520, 0.002), (512, 1600, 0.002)]
+         (128, 64, 0.3), (200, 20, 0.9), (300, 12, 0.8), (340, 12, 0.8),
+         (1600, 520, 0.002), (512, 1600, 0.002)]
 
 
 def _by_shifts(nx, ny, r, x):
