@@ -18,6 +18,11 @@ constexpr int kMaxLevels = 16;      // multigrid levels (level 0 = the element g
 constexpr int kBarLine = 64;        // words per barrier counter (one 256-B line each)
 constexpr int kBarParts = 8;        // counters per group barrier (workgroup b arrives at b % 8)
 constexpr int kBarStride = kBarLine * kBarParts;  // words per group's barrier
+// resident lanes
+constexpr int kResMaxDeg = 8;             // degree of the preconditioner's polynomial
+constexpr int kResRows = 6;               // most rows of a window column per thread
+constexpr int kResGroup = kMaxGroup / 2;  // workgroups per resident group, at most
+constexpr int kRim = 2;                   // cells around the window per thread
 
 // Lane kinds: a lane is a sequence of linear solves executed by one group of
 // workgroups; lanes of one launch run concurrently and meet only through flags.

@@ -48,10 +48,7 @@ namespace pt {
 
 namespace {
 
-constexpr int kResMaxDeg = 8;        // degree of the preconditioner's polynomial
-constexpr int kResRows = 6;         // most rows of a window column per thread
 constexpr int kResSums = 8;         // sums per reduction, at most
-constexpr int kResGroup = kMaxGroup / 2;  // workgroups per resident group, at most
 
 // Sum over the 64 lanes of a wave, in every lane, in a fixed order: within rows
 // of 16 lanes by data-parallel moves, then the four row sums.
@@ -205,8 +202,6 @@ struct ResTimers {
     unsigned long long work = 0, bar = 0, red = 0, flag = 0;
     long long mark = 0;
 };
-
-constexpr int kRim = 2;  // rim cells per thread
 
 // What one thread holds of its workgroup's window: its column gx, rows gy0 ..
 // gy0 + NR - 1, and the node sets as bits per row: live (in the grid, the window
