@@ -243,7 +243,10 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
             return true;
         }
     }
-    if (!own || (nb > 0 && (avail < 1 || (avail < nb && (!share || nb > 2))))) return false;
+    // (a sweep that is its launch's only lane needs no group beside it, but has to fit:
+    // the cold coarse-mesh sweep takes 260 workgroups at 1500 x 1500 elements)
+    if (!own || lat > grid) return false;
+    if (nb > 0 && (avail < 1 || (avail < nb && (!share || nb > 2)))) return false;
     avail = std::min(avail, lanes);
     const int gsz = g_min > 0 ? std::max(g_min, (grid - lat) / std::max(1, avail)) : 1;
     int left = avail, kinds = nb;

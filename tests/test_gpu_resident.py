@@ -107,3 +107,17 @@ def test_coarse_mesh_lanes(gpu, nx, ny, tuning):
     print("warm", e, g["status"], flush=True)
     assert g["status"]["status"] == 0
     assert max(e.values()) <= 1e-10
+
+
+def test_cold_coarse_mesh_sweep_beyond_the_grid_streams(gpu):
+    """A cold coarse-mesh sweep that no group of the device holds runs as streaming
+    lanes do, with the same bits (two window rows per thread: the device holds
+    760 x 760 elements, 770 x 770 no more)."""
+    cfg = _cfg(nx=770, ny=770, n_steps=2, n_slices=2, t_final=0.001, cg_rtol=1e-6, propagator=2)
+    rho = density_uniform_noise(770, 770, 9)
+    a = run_gpu(dict(cfg, tuning=dict(resident_npt_max=2)), rho, with_status=True)
+    b = run_gpu(dict(cfg, tuning=dict(resident=0)), rho, with_status=True)
+    print(a["status"], b["status"], flush=True)
+    assert a["status"]["status"] == b["status"]["status"] == 0
+    for k in ("S", "uT", "lam", "grad"):
+        assert np.array_equal(a[k], b[k]), k
