@@ -50,6 +50,22 @@ namespace {
 
 constexpr int kResSums = 8;         // sums per reduction, at most
 
+// A solve ends its rounds at this share of cg_rtol ||b||. What few rounds of the
+// polynomial leave of a residual are its lowest modes, with more error to a residual
+// than what a Jacobi CG leaves, which is spread over the spectrum; and what an
+// extrapolated start leaves has the same sign at every step and adds up over a slice.
+// Errors at shares of 1, against Jacobi CG on streaming lanes at the same cg_rtol
+// (warm cycles of 14 problems of 32^2 to 512^2): Theta up to 144 times and states up
+// to 9 times; with these shares states, multipliers and gradients are 0.02 to 0.1 of
+// them at 1e-4 to 1e-12 (geometric means). A start within cg_rtol itself ends a
+// solve as before. 256^2, 32 slices, warm, cg_rtol 1e-12: 29.0 -> 30.1 ms; sequential
+// 100^2, 240 steps: 28.8 -> 34.1 ms.
+constexpr double kStopFine = 0.1, kStopCoarse = 0.3;
+// Solves again from the true residual, at most. Near what FP64 can certify each try
+// rounds anew: 384^2, Gaussian design, cg_rtol 1e-12 was reported as PT_ENOCONV at
+// shares of 1 and 2 tries.
+constexpr int kResRestarts = 4;
+
 // Sum over the 64 lanes of a wave, in every lane, in a fixed order: within rows
 // of 16 lanes by data-parallel moves, then the four row sums.
 template <int CTRL>
@@ -1135,7 +1151,7 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
     ResLaneCtx x;
     Control *ctl;
     long long tmo;
-    double rtol;
+    double rtol, stop;
     int max_iter, coarse_iters, max_restarts;
     bool verify;
     int rows;
@@ -1149,7 +1165,8 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         max_iter = C.max_iter;
         coarse_iters = fine || CM ? 0 : C.coarse_iters;
         verify = CM || C.verify || C.fp32;
-        max_restarts = CM ? 3 : C.fp32 ? C.max_restarts : 2;
+        stop = rtol * (fine ? kStopFine : kStopCoarse);
+        max_restarts = !CM && C.fp32 ? C.max_restarts : kResRestarts;
         x.D = Dp;
         x.gv0 = group_vec(B, G.vec, V_R0);
         x.gvs = B.pool_stride;
@@ -1514,7 +1531,9 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
 #pragma unroll
                 for (int k = 0; k < NR; ++k) lds[LX + k * kThreads] = 0.0;
             } else {
-                closed = rnorm <= rtol * bnorm;
+                // (an extrapolated start is never the solution: its error has the same
+                // sign at every step)
+                closed = x.order > 0 ? rnorm == 0.0 : rnorm <= rtol * bnorm;
             }
         } else {
             put_sums(sum);
@@ -1554,7 +1573,7 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
             // solve can start at once (a round gains about a decimal digit)
             ++iter;
             shown = trunc ? iter >= coarse_iters
-                          : rnorm <= 200.0 * rtol * bnorm || iter >= max_iter;
+                          : rnorm <= 200.0 * stop * bnorm || iter >= max_iter;
             if (shown) publish_x(step);
             put_sums(sum);
             if (!barrier(false)) return false;
@@ -1562,7 +1581,7 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
             get_sums(sum);
             rnorm = sqrt(sum[2]);
             if (trunc ? (iter >= coarse_iters || rnorm == 0.0)
-                      : (rnorm <= rtol * bnorm || iter >= max_iter)) {
+                      : (rnorm <= stop * bnorm || iter >= max_iter)) {
                 relres = bnorm > 0.0 ? rnorm / bnorm : 0.0;
                 capped = !trunc && !(rnorm <= rtol * bnorm);
                 if (capped && rnorm > rtol * bnorm && leader) set_status(ctl, -4);
