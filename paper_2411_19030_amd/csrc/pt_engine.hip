@@ -995,11 +995,16 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
             //
             // A pass is bound by the latency of its loads (512^2 nodes on 8
             // workgroups: 64 nodes a thread, 0.35 TB/s from memory, vector units
-            // 10% busy), so no load stands in a branch of its own, where its use
-            // would wait for it: nodes outside read a node inside, and all loads
-            // of kG nodes are in flight together. 39 -> 29 us per pass of 22
-            // such groups (6 nodes: with 8 the kernel spills).
-            constexpr int kG = sizeof(Real) == 4 ? 6 : 4;
+            // 10% busy), so a value is used in no branch with its load, where the
+            // use would wait for it, and all loads of kG nodes are in flight
+            // together. Nodes behind a range load nothing: on small grids most of
+            // a thread's kG nodes are there, and with loads of a node inside in
+            // their place 32^2 took 26.9 ms (FP64) and 32.9 (FP32) against 23.1
+            // and 24.4 with a load of its own per node; so it takes 22.3 and 21.9.
+            // 512^2 on such groups: 584 ms with a load of its own per node, 497
+            // with one node at a time, 446 with two, 416 with three, 411 with four
+            // (32^2 then 25.1), 430 with six.
+            constexpr int kG = 3;
             auto staged = [&](int l, const Real *v, const Real *e, int a, int b, auto &&ld,
                               auto &&opf) {
                 constexpr int N = kG;
@@ -1044,7 +1049,8 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                     for (int id0 = c0 + threadIdx.x; id0 < c1; id0 += kThreads * N) {
                         decltype(ld(0)) vals[N];
 #pragma unroll
-                        for (int u = 0; u < N; ++u) vals[u] = ld(min(id0 + u * kThreads, c1 - 1));
+                        for (int u = 0; u < N; ++u)
+                            if (u == 0 || id0 + u * kThreads < c1) vals[u] = ld(id0 + u * kThreads);
 #pragma unroll
                         for (int u = 0; u < N; ++u) {
                             const int id = id0 + u * kThreads;
@@ -1065,7 +1071,8 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                 for (int id0 = a + threadIdx.x; id0 < b; id0 += kThreads * N) {
                     decltype(ld(0)) vals[N];
 #pragma unroll
-                    for (int u = 0; u < N; ++u) vals[u] = ld(min(id0 + u * kThreads, b - 1));
+                    for (int u = 0; u < N; ++u)
+                        if (u == 0 || id0 + u * kThreads < b) vals[u] = ld(id0 + u * kThreads);
 #pragma unroll
                     for (int u = 0; u < N; ++u) {
                         const int id = id0 + u * kThreads;
@@ -1136,7 +1143,7 @@ __global__ void __launch_bounds__(kThreads) k_engine(const EngineDesc *__restric
                     stc(lr(l + 1) + I, rc);
                     stc(la(l + 1) + I, x.c != (Real)0 ? om * rc / x.c : (Real)0);
                 };
-                nodes(std::integral_constant<int, kG / 2>{}, a, b, ld, put);
+                nodes(std::integral_constant<int, 2>{}, a, b, ld, put);
             };
 
             // pointwise CG update (u of the previous round is in UB0) and the
