@@ -216,7 +216,8 @@ k_filter_scale_rect(Geom g, double beta, double eta, const double *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Larger windows: one thread per element, the neighbourhood through the caches
+// Larger windows, and few elements: one thread per element, the neighbourhood
+// through the caches
 // ---------------------------------------------------------------------------
 
 __global__ void k_filter_forward(Geom g, double beta, double eta, const double *__restrict__ chi,
@@ -308,6 +309,29 @@ SumPlan sum_plan(const Geom &g) {
     return P;
 }
 
+// Whether one thread per element takes less time than the tiles, for a direction of
+// `sums` sums per element (the backward one also sums the weights). Where the tiles do
+// not fill the device both are chains: one thread's terms, each 0.11 us or, with many
+// elements, the time of them all; a tile's column distances, 1 us and 0.17 us per T
+// rows of the window, for each piece of rows that is staged. Forward, us, one thread
+// per element against tiles:
+//    100^2, r = 0.03 (49 terms, the paper's filter)   11 against 16
+//    199 x 150, r = 0.03 (99)                         16 against 28
+//    16384 x 1, r = 0.01 (327 in a row)               40 against 287
+//    300 x 12, r = 0.8 (3600)                        404 against 707
+//    256^2, r = 0.03 (225)                            31 against 25
+//    64^2, r = 0.2 (625)                              74 against 38
+bool direct_pays(const Geom &g, const SumPlan &P, int sums) {
+    const int rows = kWaves * P.T;
+    const long long tiles = (long long)((g.nx + kTX - 1) / kTX) * ((g.ny + rows - 1) / rows);
+    if (tiles > 256) return false;
+    const double terms = (double)std::min(2 * g.Rx + 1, g.nx) * std::min(2 * g.Ry + 1, g.ny);
+    const double term = std::max(0.11, 1.33e-6 * (double)g.nx * g.ny);
+    const int pieces = (rows + 2 * g.Ry + P.rc - 1) / P.rc;
+    const double tile = 8.5 + pieces * (g.Rx + 1) * (1.0 + 0.17 * ((2 * g.Ry + 2 * P.T - 1) / P.T));
+    return sums * (5.0 + terms * term) < tile + 4.0 * (sums - 1);
+}
+
 template <bool ADJ>
 int launch_sum(const Geom &g, const SumPlan &P, double beta, double eta, const double *x,
                double *fil, double *out, hipStream_t stream) {
@@ -338,7 +362,7 @@ extern "C" int pt_filter_projection(const pt_filter *f, const double *chi, doubl
         overlap(chi_fil, n, chi_phys, n))
         return PT_EINVAL;
     const SumPlan P = sum_plan(g);
-    if (P.T > 0)
+    if (P.T > 0 && !direct_pays(g, P, 1))
         return launch_sum<false>(g, P, f->beta, f->eta, chi, chi_fil, chi_phys, stream);
     const dim3 grid((g.nx + kBX - 1) / kBX, (g.ny + kBY - 1) / kBY), block(kBX, kBY);
     hipLaunchKernelGGL(k_filter_forward, grid, block, 0, stream, g, f->beta, f->eta, chi, chi_fil,
@@ -357,7 +381,7 @@ extern "C" int pt_filter_projection_backward(const pt_filter *f, const double *c
         overlap(grad_chi, n, grad_phys, n))
         return PT_EINVAL;
     const SumPlan P = sum_plan(g);
-    if (P.T > 0) {
+    if (P.T > 0 && !direct_pays(g, P, 2)) {
         const size_t lds = sizeof(double) * rect_doubles(g);
         if (hipFuncSetAttribute((const void *)k_filter_scale_rect,
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
