@@ -362,6 +362,7 @@ typedef struct pt_batch_tuning {
     int32_t sweep_wgs;     /* workgroups per sweep group, 1..1024                             */
     int32_t sweep_groups;  /* sweep groups, >= 1                                              */
     int32_t resident;      /* 1: vectors held in registers (every design's tile must fit)   */
+                           /* on groups of more workgroups where a design's windows need them */
     int32_t grid;          /* workgroups of the launch, 0 = as many as are co-resident        */
     int32_t tile_max;      /* streaming (resident = 0): largest node tile a workgroup stages  */
                            /* per pass, 256..16384, or 0 for the built-in 4096               */
