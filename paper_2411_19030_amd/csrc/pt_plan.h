@@ -91,11 +91,17 @@ bool res_shape(int W, int HN, int max_wg, int deg, int rows_max, size_t lds_cap,
 // the convergence falls off by some 3% per degree. More applications per round pay
 // until the window's rings need more rows (101^2 nodes, sequential: 105 ms at degree 3,
 // 71 at 8; sweep of 30 slices 13.2 ms at 4, 11.5 at 6).
-bool res_fit(int W, int HN, int max_wg, int d0, int rows_max, size_t cap, Shape &s, int &n) {
+// `more` false: that degree only. Coarse-mesh solves are well conditioned, with 6 to 24
+// rounds at degree 4, and the search gives their passes 0 to 5% warm, up to 12% cold
+// (256^2 with 8 slices: 9.15 against 9.02 ms, 12.3 against 11.0); but it leaves them
+// so few rounds, 4 on 17^2 nodes as the fine solves take, that an iteration cap hardly
+// tells them apart any more.
+bool res_fit(int W, int HN, int max_wg, int d0, int rows_max, size_t cap, Shape &s, int &n,
+             bool more = true) {
     bool ok = false;
     for (int deg = d0; deg >= 0 && !ok; --deg)
         ok = res_shape(W, HN, max_wg, deg, rows_max, cap, s, n);
-    if (!ok || d0 < 2 || s.deg < d0) return ok;
+    if (!ok || !more || d0 < 2 || s.deg < d0) return ok;
     auto cost = [](int nr, int apps) {
         return (3.0 + 0.5 * nr + apps * (0.1 + 0.12 * nr)) / apps * (1.0 + 0.03 * apps);
     };
@@ -146,18 +152,14 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
     const int deg_f = 3, deg_c = 4;
     auto deg_of = [&](int kind) {
         if (kind == F_PRI || kind == F_ADJ) return deg_f;
-        // Coarse-mesh solves are better conditioned: at degree 4 those of 17^2 nodes
-        // take 6 rounds, no more than the fine ones, so that an iteration cap that
-        // just passes the fine solves would no longer report the coarse ones. Small
-        // meshes keep degree 1 (such a pass is bound by its fine lanes), larger ones
-        // 3 (129^2 nodes at degree 4: 22 rounds against 9).
-        if (is_cm_kind(kind)) return (C.nx / 2) * (C.ny / 2) <= 48 * 48 ? 1 : deg_f;
+        if (is_cm_kind(kind)) return deg_c;
         return C.coarse_iters > 0 ? 0 : deg_c;
     };
     auto rows_of = [&](int kind) { return is_cm_kind(kind) ? C.ny / 2 + 1 : HN; };
     auto width_of = [&](int kind) { return is_cm_kind(kind) ? C.nx / 2 + 1 : C.W; };
     auto fit = [&](int kind, int max_wg, Shape &s, int &n) {
-        return res_fit(width_of(kind), rows_of(kind), max_wg, deg_of(kind), rows_max, cap, s, n);
+        return res_fit(width_of(kind), rows_of(kind), max_wg, deg_of(kind), rows_max, cap, s, n,
+                       !is_cm_kind(kind));
     };
     auto min_wgs = [&](int kind, int deg) {
         return res_min_wgs(width_of(kind), rows_of(kind), deg, rows_max, cap);

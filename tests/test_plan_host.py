@@ -79,3 +79,9 @@ def test_accepted_plans_fit_the_device(ask):
     assert sum(a[0] for a in got) > 500
     for l, a in zip(lines, got):
         assert not a[0] or 0 < plan_workgroups(a) <= GRID, (l, a)
+
+
+def test_coarse_mesh_degree_does_not_depend_on_the_size(ask):
+    sizes = [4, 16, 32, 48, 64, 94, 96, 98, 100, 128, 160, 200, 256, 400]
+    got = ask([plan(n, n, 8, [lane(CM_SWEEP_PRI, 1, latency=1, fixed=24)], cm=1) for n in sizes])
+    assert {n: a[7] for n, a in zip(sizes, got)} == {n: 4 for n in sizes}
