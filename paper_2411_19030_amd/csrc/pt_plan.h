@@ -41,15 +41,35 @@ struct LanePlan {
 // Window rows per thread the kernel is built for.
 constexpr int kResRowChoices[] = {2, 4, 6};
 static_assert(kResRowChoices[2] == kResRows, "the largest variant");
-constexpr int kResMaxColumns = 480;  // window columns: two rim cells per thread at most
+constexpr int kResMaxColumns = 480;  // columns of a window, at most
+static_assert(kResMaxColumns <= kThreads, "a thread for each");
+
+// A workgroup's window: the rectangle with its rings where the grid is cut, and the
+// rows of it that the threads hold.
+struct Window {
+    int wc, wr, rows;
+    Window(const Shape &s, int W, int HN)
+        : wc(s.tw + (s.tw < W ? 2 * (s.deg + 1) : 0)),
+          wr(s.th + (s.th < HN ? 2 * (s.deg + 1) : 0)),
+          rows(wc > kResMaxColumns ? 0 : std::min(kThreads / wc, (wr + s.nr - 1) / s.nr) * s.nr) {}
+};
 
 // LDS bytes of a resident lane: two operand windows with a rim and two values
 // per node slot (the p and x of the solve).
 size_t res_lds_bytes(const Shape &s, int W, int HN) {
-    const int hx = s.tw < W ? s.deg + 1 : 0, hy = s.th < HN ? s.deg + 1 : 0;
-    const int wc = s.tw + 2 * hx, wr = s.th + 2 * hy;
-    const int nq = std::min(kThreads / wc, (wr + s.nr - 1) / s.nr);
-    return sizeof(double) * (2 * (size_t)(wc + 2) * (nq * s.nr + 2) + 2 * (size_t)s.nr * kThreads);
+    const Window w(s, W, HN);
+    return sizeof(double) *
+           (2 * (size_t)(w.wc + 2) * (w.rows + 2) + 2 * (size_t)s.nr * kThreads);
+}
+
+// Whether a workgroup holds its window of a shape: the threads its rows, the LDS its
+// operands, and kRim cells per thread the cells around it (those above and below first;
+// where the grid is not cut into columns the ones beside it lie outside).
+bool res_window_fits(const Shape &s, int W, int HN, size_t lds_cap) {
+    const Window w(s, W, HN);
+    return w.wc <= kResMaxColumns && w.wr <= w.rows &&
+           2 * (w.wc + 2) + (s.tw < W ? 2 * w.rows : 0) <= kRim * kThreads &&
+           res_lds_bytes(s, W, HN) <= lds_cap;
 }
 
 // The rectangles for a grid of W x HN nodes on at most max_wg workgroups: the
@@ -63,15 +83,12 @@ bool res_shape(int W, int HN, int max_wg, int deg, int rows_max, size_t lds_cap,
         for (int TX = 1; TX <= std::min(max_wg, W); ++TX) {
             const int tw = (W + TX - 1) / TX;
             if ((W + tw - 1) / tw != TX) continue;  // the same width with fewer columns
-            const int wc = tw + (TX > 1 ? 2 * (deg + 1) : 0);
-            if (wc > kResMaxColumns) continue;
             const int th = (HN + std::min(max_wg / TX, HN) - 1) / std::min(max_wg / TX, HN);
             const int TY = (HN + th - 1) / th;
-            const int wr = th + (TY > 1 ? 2 * (deg + 1) : 0);
-            if (wr > kThreads / wc * nr) continue;
             const Shape s{0, tw, th, deg, nr};
-            if (res_lds_bytes(s, W, HN) > lds_cap) continue;
-            const double cost = (double)wc * wr;
+            if (!res_window_fits(s, W, HN, lds_cap)) continue;
+            const Window w(s, W, HN);
+            const double cost = (double)w.wc * w.wr;
             if (cost < best_cost) {
                 best_cost = cost;
                 best = s;
@@ -131,7 +148,7 @@ int res_min_wgs(int W, int HN, int deg, int rows_max, size_t lds_cap) {
             if (wc > kResMaxColumns) continue;
             const int wr = kThreads / wc * nr;
             const int th = HN <= wr ? HN : wr - 2 * (deg + 1);
-            if (th < 1 || res_lds_bytes(Shape{0, tw, th, deg, nr}, W, HN) > lds_cap) continue;
+            if (th < 1 || !res_window_fits(Shape{0, tw, th, deg, nr}, W, HN, lds_cap)) continue;
             const int n = TX * ((HN + th - 1) / th);
             if (best == 0 || n < best) best = n;
         }

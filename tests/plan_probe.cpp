@@ -2,6 +2,7 @@
 // tests/test_plan_host.py. Reads one request per line from stdin and answers each
 // with one line:
 //   shape W HN max_wg deg rows      -> ok tw th deg nr wgs lds | min_wgs
+//   window W HN tw th deg nr        -> fits lds
 //   plan nx ny Ntau M grid rows sweep_wgs share cm, then 9 numbers per kind of lane
 //        (kind count slice0 dir weight latency queues fixed_nwg lead_kind)
 //                                   -> ok one_queue lds, then per kind of lane
@@ -25,6 +26,14 @@ static void shape(std::istream &in) {
     std::cout << ok << ' ' << s.tw << ' ' << s.th << ' ' << s.deg << ' ' << s.nr << ' ' << n << ' '
               << (ok ? res_lds_bytes(s, W, HN) : 0) << ' ' << res_min_wgs(W, HN, deg, rows, cap)
               << '\n';
+}
+
+static void window(std::istream &in) {
+    int W, HN;
+    Shape s{};
+    in >> W >> HN >> s.tw >> s.th >> s.deg >> s.nr;
+    std::cout << res_window_fits(s, W, HN, kLdsDoubles * sizeof(double)) << ' '
+              << res_lds_bytes(s, W, HN) << '\n';
 }
 
 static void plan(std::istream &in) {
@@ -63,6 +72,7 @@ int main() {
         std::istringstream in(line);
         in >> what;
         if (what == "shape") shape(in);
+        else if (what == "window") window(in);
         else plan(in);
     }
 }

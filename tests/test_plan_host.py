@@ -85,3 +85,47 @@ def test_coarse_mesh_degree_does_not_depend_on_the_size(ask):
     sizes = [4, 16, 32, 48, 64, 94, 96, 98, 100, 128, 160, 200, 256, 400]
     got = ask([plan(n, n, 8, [lane(CM_SWEEP_PRI, 1, latency=1, fixed=24)], cm=1) for n in sizes])
     assert {n: a[7] for n, a in zip(sizes, got)} == {n: 4 for n in sizes}
+
+
+THREADS, RIM = 512, 2
+
+
+def rim_cells_lost(W, HN, tw, th, deg, nr):
+    """Cells around the windows of a shape's tiles that lie in the grid and have an
+    index beyond what the threads hold: the rows above and below first, then the two
+    columns beside the rows, in turn (the kernel's order)."""
+    TX, TY = -(-W // tw), -(-HN // th)
+    hx, hy = (deg + 1 if TX > 1 else 0), (deg + 1 if TY > 1 else 0)
+    wc, wr = tw + 2 * hx, th + 2 * hy
+    rows = min(THREADS // wc, -(-wr // nr)) * nr
+    sz = wc + 2
+    lost = 0
+    for ty in {0, TY // 2, TY - 1}:
+        for tx in {0, TX // 2, TX - 1}:
+            for e in range(RIM * THREADS, 2 * sz + 2 * rows):
+                if e < 2 * sz:
+                    cx, cy = e % sz, 0 if e < sz else rows + 1
+                else:
+                    cx, cy = (sz - 1 if e & 1 else 0), 1 + ((e - 2 * sz) >> 1)
+                gx, gy = tx * tw - hx - 1 + cx, ty * th - hy - 1 + cy
+                lost += 0 <= gx < W and 0 <= gy < HN and cy <= wr + 1
+    return lost
+
+
+def test_windows_that_fit_lose_no_cell_of_their_rim(ask):
+    rng = random.Random(11)
+    cases = [(4, 1300, 1, 600, 1, 6), (2, 1300, 1, 1000, 0, 6), (9, 1300, 3, 600, 0, 6),
+             (4, 1300, 4, 600, 1, 6), (300, 2, 300, 2, 3, 2), (900, 3, 450, 3, 3, 6)]
+    for _ in range(3000):
+        W, HN = (int(2 ** rng.uniform(1, 11)) for _ in range(2))
+        tw = max(1, int(W / 2 ** rng.uniform(0, 8)))
+        th = max(1, int(HN / 2 ** rng.uniform(0, 8)))
+        cases.append((W, HN, tw, th, rng.randrange(9), rng.choice([2, 4, 6])))
+    got = ask(["window " + " ".join(map(str, c)) for c in cases])
+    assert [g[0] for g in got[:6]] == [0, 0, 0, 1, 1, 1]
+    assert sum(g[0] for g in got) > 500
+    for c, g in zip(cases, got):
+        if g[0]:
+            assert rim_cells_lost(*c) == 0, c
+            assert g[1] <= 160 * 1024 - 1024, c
+    assert rim_cells_lost(*cases[0]) > 0 and rim_cells_lost(*cases[2]) > 0
