@@ -445,9 +445,9 @@ __device__ __forceinline__ void res_mass(const ResGeo &g, int z, const double (&
 // (ctx.step > 0), then right-hand side, start and residual of the next one. The
 // residual r0 of the thread's nodes is left in their cells of window 1. Returns
 // false when a wait timed out or another workgroup aborted.
-template <int NR>
+template <int NR, bool TIMED>
 __device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, const ResCoef<NR> &A,
-                                          const double (&cc)[NR]) {
+                                          const double (&cc)[NR], ResTimers &tm) {
     extern __shared__ double lds[];
     const ResGeo g = geo;
     auto is = [](unsigned m, int k) { return ResGeo::is(m, k); };
@@ -485,7 +485,18 @@ __device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, cons
         x.st_jprev = st.jprev;
     }
     // waits: the guess of a cold-started slice; what a sweep's step reads
-    auto waitf = [&](int idx) { return wait_flag(B.flags, idx, I.epoch, ctl, tmo); };
+    auto waitf = [&](int idx) -> bool {
+        if constexpr (TIMED) {
+            const long long t0 = now_ticks();
+            const bool ok = wait_flag(B.flags, idx, I.epoch, ctl, tmo);
+            const long long t1 = now_ticks();
+            tm.work += t0 - tm.mark;
+            tm.flag += t1 - t0;
+            tm.mark = t1;
+            return ok;
+        }
+        return wait_flag(B.flags, idx, I.epoch, ctl, tmo);
+    };
     if (next && st.wait) {
         if (!waitf(st.wait_idx)) return false;
         if (L.kind == F_PRI && I.cold && L.slice > 0)
@@ -1445,7 +1456,7 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
             if constexpr (CM) {
                 if (!res_setup_cm<NR>(q, x, A, cc)) return false;
             } else {
-                if (!res_setup<NR>(q, x, A, cc)) return false;
+                if (!res_setup<NR, TIMED>(q, x, A, cc, tm)) return false;
             }
         } else {
             res_residual<NR>(q, x, A, cc);
