@@ -257,7 +257,8 @@ int pt_sensitivities(const pt_problem *prob, const double *rho, const void *ws,
  * and copies up to out_words 64-bit words: n_lanes records of `stride` words,
  * each [kind, slice, workgroups, tile, group barriers, CG iterations,
  * start tick, ticks working, ticks in barriers, ticks reducing, ticks waiting
- * on other lanes, unused, end tick of step 0, 1, ...], ticks of the device's
+ * on other lanes, window rows per thread + 256 x polynomial degree of a
+ * resident lane (else 0), end tick of step 0, 1, ...], ticks of the device's
  * 100 MHz real-time clock; unused records are zero. Lane kinds: 0 fine primal,
  * 1 batched coarse primal, 2 primal sweep, 3 cold primal sweep, 4-7 the adjoint
  * counterparts.

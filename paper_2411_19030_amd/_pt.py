@@ -449,7 +449,8 @@ def pt_query_trace(prob: Problem, ws, stream=None) -> list:
                         tile=int(r[3]), rounds=int(r[4]), iters=int(r[5]),
                         start_us=(int(r[6]) - t0) / 100.0, step_end_us=steps,
                         work_us=int(r[7]) / 100.0, barrier_us=int(r[8]) / 100.0,
-                        reduce_us=int(r[9]) / 100.0, flag_us=int(r[10]) / 100.0))
+                        reduce_us=int(r[9]) / 100.0, flag_us=int(r[10]) / 100.0,
+                        rows=int(r[11]) % 256, degree=int(r[11]) // 256))
     return out
 
 

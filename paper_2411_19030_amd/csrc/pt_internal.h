@@ -253,6 +253,7 @@ enum {
     TR_T_BAR,     // ticks inside group barriers (drain + arrival + wait)
     TR_T_RED,     // ticks reading partial sums after barriers
     TR_T_FLAG,    // ticks waiting on other lanes' flags
+    TR_SHAPE,     // resident lanes: window rows per thread + 256 x polynomial degree, else 0
     TR_HDR = 12
 };
 

@@ -1423,6 +1423,7 @@ __device__ __forceinline__ bool res_lane(const EngineDesc *Dp, const Lane L, con
         trec[TR_SLICE] = L.slice;
         trec[TR_NWG] = g;
         trec[TR_TILE] = L.tw * L.th;
+        trec[TR_SHAPE] = (unsigned long long)(NR + 256 * deg);
         trec[TR_START] = (unsigned long long)now_ticks();
     }
 

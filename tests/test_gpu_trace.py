@@ -1,7 +1,12 @@
-"""The lane trace of resident lanes: times spent waiting on other lanes' flags."""
+"""The lane trace of resident lanes: times spent waiting on other lanes' flags, and the
+window rows per thread and polynomial degree of a lane, by which the tests below know
+that each instance of the kernel ran.
+
+Bar: 1e-10 on every output at cg_rtol 1e-13, as in tests/test_gpu_resident.py."""
+import numpy as np
 import pytest
 
-from tests.gpu_helpers import run_gpu
+from tests.gpu_helpers import compare, run_gpu, run_oracle
 from workloads import density_uniform_noise
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +27,34 @@ def test_flag_waits_are_told_apart_from_work(gpu, resident):
     print(first, total, parts, flush=True)
     assert sweep["flag_us"] >= 0.5 * (first - sweep["start_us"])
     assert 0.8 * total <= sum(parts) <= 1.1 * total
+
+
+# grid, slices, sweep workgroups; window rows per thread of the fine (and batched coarse)
+# lanes and of the sweep: tiles cut one way and both, with a ragged last one
+ROWS = [(61, 44, 12, 8, 2, 2), (61, 44, 24, 4, 4, 4), (97, 65, 24, 4, 4, 6),
+        (61, 130, 12, 8, 4, 4), (90, 74, 24, 4, 6, 6), (127, 96, 24, 8, 6, 6)]
+
+
+@pytest.mark.parametrize("nx,ny,n_slices,sweep_wgs,fine,sweep", ROWS)
+def test_each_number_of_window_rows_runs(gpu, nx, ny, n_slices, sweep_wgs, fine, sweep):
+    """Many slices leave a lane few workgroups, and so many window rows per thread."""
+    cfg = dict(nx=nx, ny=ny, n_steps=6 * n_slices, n_slices=n_slices, pnorm=8, cg_rtol=1e-13,
+               max_iter=20000, tuning=dict(sweep_wgs=sweep_wgs))
+    rho = density_uniform_noise(nx, ny, nx + 5 * ny)
+    o = run_oracle(cfg, rho)
+    guess = (o["uT"], o["utheta"], o["lam"])
+    rho = np.clip(rho + 0.02, 0.0, 1.0)
+    g = run_gpu(cfg, rho, guess, with_status=True, with_trace=True)
+    e = compare(g, run_oracle(cfg, rho, guess))
+    shapes = {(r["kind"], r["rows"], r["degree"]) for r in g["trace"]}
+    print(nx, ny, n_slices, e, sorted(shapes), g["status"], flush=True)
+    rows = {k: {r for q, r, _ in shapes if q == k} for k in ("F_ADJ", "GK_ADJ", "SWEEP_ADJ")}
+    assert fine in rows["F_ADJ"] and rows["GK_ADJ"] == {fine} and rows["SWEEP_ADJ"] == {sweep}
+    assert g["status"]["status"] == 0
+    assert max(e.values()) <= 1e-10
+
+
+def test_streaming_lanes_have_no_window(gpu):
+    cfg = dict(nx=32, ny=32, n_steps=8, n_slices=2, tuning=dict(resident=0))
+    tr = run_gpu(cfg, density_uniform_noise(32, 32, 5), with_trace=True)["trace"]
+    assert {(r["rows"], r["degree"]) for r in tr} == {(0, 0)}
