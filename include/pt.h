@@ -81,9 +81,10 @@ enum { PT_PARAREAL = 0, PT_PLT = 1, PT_COARSE_MESH = 2 };
  * environment variables. */
 typedef struct pt_tuning {
     int32_t wg_per_cu;         /* engine workgroups per compute unit                        (1)  */
-    int32_t resident;          /* -1: resident groups (vectors in registers) where they pay;    */
-                               /*  0: streaming groups only; 1: resident wherever they fit  (-1) */
-    int32_t resident_npt_max;  /* most window rows per thread of resident lanes, 1..8       (8)  */
+    int32_t resident;          /* -1, 1: resident lanes (vectors in registers) wherever they    */
+                               /*  fit; 0: streaming groups only                            (-1) */
+    int32_t resident_npt_max;  /* most window rows per thread of resident lanes, 1..8: 2, 4  */
+                               /* or 6 are used, 1 counts as 2                               (8)  */
     int32_t sweep_wgs;         /* workgroups of a correction-sweep group; 0: by problem size (0) */
     int32_t cm_sweep_wgs;      /* workgroups of a coarse-mesh correction-sweep group        (24) */
     int32_t fine_wgs;          /* > 0: fine lanes on groups of this many workgroups, alike  */
@@ -129,7 +130,11 @@ typedef struct pt_problem {
     int32_t pnorm;             /* p, even >= 2                                      (Eq. 2.11)     */
     int32_t iterations;        /* Parareal iterations per pass, >= 1 (1 = one-shot, Alg. 3)       */
     double cg_rtol;            /* stop when ||b - A x||_2 <= cg_rtol ||b||_2, per system, > 0     */
-    int32_t max_iter;          /* CG iteration cap per solve, >= 1                                */
+                               /* (resident lanes go on to 0.1 of it in fine solves, 0.3 in coarse) */
+    int32_t max_iter;          /* CG iteration cap per solve, >= 1; an iteration applies the     */
+                               /* preconditioner once, which on resident lanes is a polynomial of */
+                               /* the operator: one does the work of several Jacobi-PCG iterations, */
+                               /* so a cap that ends streaming solves may not end resident ones  */
     int32_t precision;         /* PT_FP64, or PT_FP32_REFINE: FP32 CG (stencil, vectors, halo)    */
                                /* with FP64 dot products, FP64 x and FP64 residual refinement     */
     int32_t precond;           /* PT_JACOBI, or PT_GMG: geometric multigrid V(1,1) cycle (Galerkin */
@@ -142,7 +147,7 @@ typedef struct pt_problem {
     const uint8_t *dirichlet_mask; /* HOST, (nx+1)(ny+1) bytes, read when bc == PT_BC_MASK        */
     int32_t propagator;        /* PT_PARAREAL (0); PT_PLT: zero coarse propagators (Sec. 7);      */
                                /* PT_COARSE_MESH: coarse propagators on an nx/2 x ny/2 mesh      */
-                               /* (nx, ny even; its coarse solves are FP64 Jacobi PCG)         */
+                               /* (nx, ny even; its coarse solves are FP64 PCG)                */
     int32_t coarse_iters;      /* 0: coarse steps solved to cg_rtol; k > 0: a cheaper coarse     */
                                /* propagator, exactly k Jacobi-PCG iterations from the step's    */
                                /* input state (PT_FP64, PT_JACOBI and PT_PARAREAL only)         */
@@ -208,7 +213,7 @@ size_t pt_state_bytes(const pt_problem *prob);
  * (P x, theta'), x the coarse backward-Euler step of size dtau from R T with
  * the load at tau_{n+1}, theta' = (theta^p + ||P x||_p^p/(N_tau N_e))^{1/p}.
  * Everything else is as with PT_PARAREAL; the coarse steps are solved to
- * cg_rtol by Jacobi PCG on one workgroup each.
+ * cg_rtol by FP64 PCG in lanes of their own.
  */
 int pt_parareal_forward(const pt_problem *prob, const double *rho, const double *guess_T,
                         const double *guess_theta, double *S, double *uT_out,

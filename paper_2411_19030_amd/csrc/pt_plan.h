@@ -157,7 +157,7 @@ int res_min_wgs(int W, int HN, int deg, int rows_max, size_t lds_cap) {
 }
 
 // Plans a launch whose lanes are all resident: group counts and sizes and the
-// lanes' shapes. False if the lanes do not fit the grid. one_queue: the sweeps
+// lanes' shapes. False if the lanes do not fit the grid. one_queue (of a plan): the sweeps
 // have no groups of their own, all lanes go through the shared queue.
 bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt_tuning &T,
                    int grid, int lds_cap_d, int sweep_wgs, const CoarseMesh *cm,
@@ -240,7 +240,6 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
         }
         const int G = g > 0 ? std::min(grid / g, lanes) : 0;
         if (G > avail) {
-            one_queue = true;
             const int gsz = grid / G;
             lds = 0;
             int used = 1;
@@ -259,6 +258,7 @@ bool plan_resident(const Consts &C, const std::vector<LanePlan> &plans, const pt
                 ngroups[k] = plans[k].kind == fk ? G : 0;
                 nwg[k] = used;
             }
+            one_queue = true;
             return true;
         }
     }

@@ -79,6 +79,7 @@ def test_accepted_plans_fit_the_device(ask):
     assert sum(a[0] for a in got) > 500
     for l, a in zip(lines, got):
         assert not a[0] or 0 < plan_workgroups(a) <= GRID, (l, a)
+        assert a[0] or not a[1], (l, a)   # what is refused asks for no shared queue
 
 
 def test_coarse_mesh_degree_does_not_depend_on_the_size(ask):
