@@ -39,8 +39,8 @@ WORKLOAD = "plain_fp64_256"
 # WRITE_SIZE runs (each scaled by what the counter reads for a 1 GiB device
 # copy: x2.0 and x1.0), averaged over the forward and adjoint launches of a warm
 # cycle; valid only for the engine sources with this hash (see profiles/).
-TRAFFIC = {"sources_sha1": "5d2b263fe4d41e5fe8c17378324e13a502dd296e",
-           "bytes_per_launch": 0.5 * (13.60e9 + 18.06e9)}
+TRAFFIC = {"sources_sha1": "ff262c266d1ecd0336206d5fd24022c2291b10a2",
+           "bytes_per_launch": 0.5 * (13.81e9 + 18.41e9)}
 
 
 def traffic_per_launch():
@@ -94,7 +94,7 @@ def parse():
                          "kind; per-round phase times on the headline) instead of the bench line")
     ap.add_argument("--autotune", action="store_true",
                     help="with --workload batch_fp32_64: run pt_autotune_batched on the batch "
-                         "(FP32+refine) and print the shape it picks (the source of BATCH_TUNING)")
+                         "(FP32+refine) and print the shape it picks")
     return ap.parse_args()
 
 
@@ -658,13 +658,11 @@ def one_shot_chain(n_cycles=30, Ntau=30) -> dict:
             "summary": summary, "rows": rows}
 
 
-# Worker shape of the 64-design batch (FP32+refine, cg_rtol 1e-7) picked by
-# pt_autotune_batched on one MI355X: `python bench.py --workload batch_fp32_64
-# --autotune` (coordinate descent over resident/streaming groups, fine and
-# sweep workgroups, sweep workers and the streaming tile; median of 3 warm
-# cycles per shape from the same saved guesses).
-BATCH_TUNING = {"fine_wgs": 4, "sweep_wgs": 8, "sweep_groups": 8, "resident": 0, "grid": 0,
-                "tile_max": 0}
+# Worker shape of the 64-design batch: None, the built-in plan (groups of a size for
+# each class of designs, resident lanes). The best shape of one kind of groups for all
+# designs that pt_autotune_batched found (4 fine and 8 sweep workgroups, 8 sweep groups,
+# streaming) takes 3.77 s per warm cycle, the built-in plan 1.65.
+BATCH_TUNING = None
 
 
 def batch_autotune(rtol=1e-7) -> dict:
@@ -694,7 +692,7 @@ def batch_compare(rtol=1e-7, ref_rtol=1e-12, accuracy=1e-6, replays=5) -> dict:
     """The 64-design workload (sides 64..512, 16..64 slices of 16 steps, seeded
     densities): one cycle of every design. Forms, each timed on a warm cycle
     after a cold one:
-    * batched FP32 + FP64 refinement in the tuned shape: all designs in one
+    * batched FP32 + FP64 refinement in the built-in shape: all designs in one
       launch per pass; timed eagerly and as the replay of the warm cycle
       captured in a HIP graph (median of `replays`; each replay is the next
       warm cycle, from the guesses the previous one saved);
@@ -779,7 +777,7 @@ def batch_compare(rtol=1e-7, ref_rtol=1e-12, accuracy=1e-6, replays=5) -> dict:
         "fp32_refine_batched": {"cg_rtol": rtol, "s_per_cycle": t32,
                                 "cell_updates_per_s": cells / t32, "max_Theta_rel_err": err32,
                                 "tuning": BATCH_TUNING,
-                                "tuning_source": "pt_autotune_batched (bench.py --autotune)",
+                                "tuning_source": "built-in (pt_batch_default_tuning)",
                                 "graph_replay_s_per_cycle": t32g,
                                 "graph_replay_cell_updates_per_s": cells / t32g,
                                 "status_ok": all(v == 0 for v in st32)},
@@ -872,7 +870,7 @@ def lane_trace(prob, rho, timers: bool) -> list:
 
 def plain_run(name: str, steps: int, warmup: int) -> dict:
     """A store-all FP64 Jacobi workload other than the headline (diff_fp64_512:
-    512 x 512, 1024 steps in 64 slices, the streaming engine): one cold cycle,
+    512 x 512, 1024 steps in 64 slices): one cold cycle,
     `warmup` untimed and `steps` timed warm cycles from its guesses, each timed
     with HIP events on the stream (forward, then adjoint + sensitivities)."""
     import torch

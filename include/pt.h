@@ -87,8 +87,8 @@ typedef struct pt_tuning {
                                /* or 6 are used, 1 counts as 2                               (8)  */
     int32_t sweep_wgs;         /* workgroups of a correction-sweep group; 0: by problem size (0) */
     int32_t cm_sweep_wgs;      /* workgroups of a coarse-mesh correction-sweep group        (24) */
-    int32_t fine_wgs;          /* > 0: fine lanes on groups of this many workgroups, alike  */
-                               /* in both passes; 0: by problem size                         (0) */
+    int32_t fine_wgs;          /* > 0: streaming fine lanes on groups of this many          */
+                               /* workgroups, alike in both passes; 0: by problem size       (0) */
     int32_t fine_groups;       /* > 0: groups for the fine lanes; 0: by their work share    (0)  */
     int32_t gk_groups;         /* > 0: groups for the batched coarse steps; 0: by share     (0)  */
     double gk_weight;          /* work of a batched coarse step relative to a fine step     (4)  */

@@ -1007,7 +1007,7 @@ int run_engine(const EngineDesc &E, const EngineDesc *D, std::vector<LanePlan> &
     return launch_engine(K, D, &E, X, grid, lds_bytes, dev, stream);
 }
 
-// Fine lanes of a single-design pass. With checkpoints (or PT_FINE_WGS set)
+// Fine lanes of a single-design pass. With checkpoints (or fine_wgs set)
 // they run on a fixed number of groups of a fixed size in both passes, so a
 // fine adjoint lane recomputes its slice's states with exactly the forward
 // pass's arithmetic, and its scratch slot (the group index) stays below
@@ -1186,8 +1186,8 @@ void batch_work(const EngineDesc &E, double &all, double &sweep) {
 // largest need; the classes and their group counts are those of the least estimated
 // time. A round is bound by latency, not by its nodes, so a group of more workgroups
 // than a design needs is wasted on it: twelve designs of 64^2 to 256^2 with 4 to 16
-// slices need 2 to 36 each (500 ms a cycle on streaming groups of 2 and 16
-// workgroups, 54 ms here). False if a design fits no group.
+// slices need 2 to 36 each (507 ms a cycle on streaming groups of 2 and 16
+// workgroups, 60 ms here). False if a design fits no group.
 bool plan_batch(std::vector<EngineDesc> &hd, int grid, int cap_d, GroupArgs &A, size_t &lds) {
     const int n = (int)hd.size();
     const size_t cap = (size_t)cap_d * sizeof(double);

@@ -107,7 +107,7 @@ bool res_shape(int W, int HN, int max_wg, int deg, int rows_max, size_t lds_cap,
 // us (measured: 5.4 at 2 rows and n = 4, 9.3 at 6 rows), and the polynomial's part in
 // the convergence falls off by some 3% per degree. More applications per round pay
 // until the window's rings need more rows (101^2 nodes, sequential: 105 ms at degree 3,
-// 71 at 8; sweep of 30 slices 13.2 ms at 4, 11.5 at 6).
+// 71 at 8; sweep of 30 slices 13.2 ms at 4, 11.5 at 6; solves ended at cg_rtol itself).
 // `more` false: that degree only. Coarse-mesh solves are well conditioned, with 6 to 24
 // rounds at degree 4, and the search gives their passes 0 to 5% warm, up to 12% cold
 // (256^2 with 8 slices: 9.15 against 9.02 ms, 12.3 against 11.0); but it leaves them

@@ -39,10 +39,10 @@
 // higher difference of them in time; the plain start's residual, formed beside
 // it, lowers the order where the states are not smooth.
 //
-// Measured at 256^2, 512 steps in 32 slices, cg_rtol 1e-12, one warm cycle,
-// against Jacobi CG on full-row tiles with one halo row: 94 -> 29.4 ms; CG
-// rounds per fine step 42 -> 8 (degree 3, extrapolated), per coarse step 169 ->
-// 36 (degree 4); sequential 100^2 with 480 steps: 741 -> 87 ms.
+// Measured at 256^2, 512 steps in 32 slices, cg_rtol 1e-12, one warm cycle, against
+// Jacobi CG on full-row tiles with one halo row: 106 -> 31.7 ms; CG rounds per fine
+// step 42 -> 8 (degree 4, extrapolated), per coarse step 169 -> 38. Sequential 100^2 with
+// 240 steps, forward and adjoint: 584 -> 78 ms.
 
 namespace pt {
 
@@ -805,8 +805,8 @@ __device__ __forceinline__ bool res_setup(const ResGeo &geo, ResLaneCtx &x, cons
 // The lanes of pt_cm_lane.hip with the solver of this file on the coarse mesh: the
 // operator's registers are formed from the coarse element values, everything around
 // the solves reads and writes the same rows. Bound by the rounds' latency as the
-// others; 256^2, 32 slices, coarse steps on 129 x 129 nodes: 100 Jacobi rounds of
-// 10.0 us per step -> 26 of 9 (degree 3), one warm cycle 68.5 -> 23.1 ms.
+// others; 256^2, 32 slices, coarse steps on 129 x 129 nodes, cg_rtol 1e-12: 100 Jacobi
+// rounds of 10.0 us per step -> 23 of 7.4 (degree 4), one warm cycle 74.2 -> 24.5 ms.
 
 // The set-up of a coarse-mesh lane: as res_setup, with the step's input u restricted
 // from fine states and the norm taken of the prolonged solution. A correction sweep's
